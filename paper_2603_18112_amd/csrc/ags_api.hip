@@ -285,6 +285,22 @@ ags_status check_device_range(const void* p, size_t bytes, const char* name, std
     return AGS_OK;
 }
 
+// Dynamic LDS with which at most `blocks` blocks fit on a CU of the device
+// (0, no cap, for blocks = 0 and if the device does not report its LDS
+// sizes).  The kernels use at most 1 KiB of static LDS.
+int lds_pad_for(int dev, int blocks) {
+    int lds_cu = 0, lds_block = 0;
+    if (blocks < 1) return 0;
+    if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
+            hipSuccess ||
+        hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    const int pad = lds_cu / (blocks + 1) + 1024;
+    return lds_cu > 0 && pad + 1024 <= lds_block && blocks * (pad + 1024) <= lds_cu ? pad : 0;
+}
+
 size_t workspace_cap() {
     const char* s = std::getenv("AGS_MAX_WORKSPACE_BYTES");
     if (!s || !*s) return (size_t)-1;
@@ -325,8 +341,9 @@ struct ags_handle {
     bool w_norm_valid = false;
     // Dynamic LDS of the fused step kernel's launches, of the statistics-only
     // step kernel's and of the LARS update kernel's (0: none), capping the
-    // blocks per CU for layouts whose w and m outgrow the Infinity Cache.
+    // blocks per CU (launch_shape).
     int lds_pad = 0, lds_pad_stats = 0, lds_pad_update = 0;
+    ags::LaunchShape shape{};
     mutable std::string err;
     bool profiling = false;
     // Per timed step: start and stop event of each kernel's dispatch.
@@ -499,7 +516,6 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
     sa.corr = h->corr();
     sa.corr_flag = h->corr_flag();
     sa.updated = fused ? 1 : 0;
-    sa.xcd_map = h->n_tiles >= ags::kXcdMapMinTiles ? 1 : 0;
     // A captured step keeps the forward direction (its replays cannot
     // alternate); the results are the same either way, only the order of
     // the tiles differs.
@@ -510,7 +526,7 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
     sa.layer_chunk_count = reinterpret_cast<unsigned*>(h->ws + h->wl.chunk_count);
     sa.lstats = h->lstats();
     sa.gstats = h->gstats();
-    sa.ew = !ew ? 0 : (16 * c.n_flat > ags::kEwStreamMinBytes ? 2 : 1);
+    sa.ew = ew ? 1 : 0;
     sa.ew_buf = h->ew_buf(0);
     sa.n_flat = c.n_flat;
     sa.ew_partials = h->ew_partials();
@@ -518,7 +534,10 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
     // carried weight norms still hold (the caller may have written w, or
     // restored a state, since the capture).
     sa.w_norm_in = (!fused && h->w_norm_valid && !capturing) ? h->w_norm() : nullptr;
-    sa.lds_pad = ew ? 0 : (fused ? h->lds_pad : h->lds_pad_stats);
+    sa.lds_pad = fused ? h->lds_pad : h->lds_pad_stats;
+    sa.stream_wm = h->shape.stream_step ? 1 : 0;
+    sa.stream_gbar = h->shape.stream_gbar ? 1 : 0;
+    sa.grouped = (!fused || h->shape.grouped_step) ? 1 : 0;
     hipError_t e = ags::launch_step(sa, c.grad_dtype, (int)h->n_tiles, fused, s, kev(0));
     if (e != hipSuccess) return launch_fail(e, "step kernel launch");
     e = ags::launch_finalize(sa, (int)h->n_chunks, s, kev(1));
@@ -545,6 +564,7 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
         ua.momentum = (float)c.momentum;
         ua.w_norm_out = (c.mode == AGS_MODE_LARS) ? h->w_norm() : nullptr;
         ua.lds_pad = h->lds_pad_update;
+        ua.stream_wm = h->shape.stream_update ? 1 : 0;
         ua.reverse = (8 * c.n_flat <= ags::kOccupancyCapMinBytes) ? 1 : 0;
         e = (c.mode == AGS_MODE_LARS) ? ags::launch_update(ua, c.grad_dtype, s, kev(2))
                                       : ags::launch_correct(ua, c.grad_dtype, s, kev(2));
@@ -718,27 +738,10 @@ ags_status ags_init(const ags_config* cfg, float* d_w, float* d_m, void* hip_str
         free_handle(h);
         return AGS_E_NOMEM;
     }
-    // Occupancy caps of the fused step kernel, the statistics-only step
-    // kernel and the LARS update kernel: LDS pads so that at most the given
-    // number of blocks fit on a CU (left off if the device does not report
-    // its LDS sizes).  The kernels use at most 1 KiB of static LDS.
-    if (8 * cfg->n_flat > ags::kOccupancyCapMinBytes) {
-        int lds_cu = 0, lds_block = 0;
-        if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
-                hipSuccess ||
-            hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
-                hipSuccess) {
-            (void)hipGetLastError();
-            lds_cu = lds_block = 0;
-        }
-        auto pad_for = [&](int blocks) {
-            const int pad = lds_cu / (blocks + 1) + 1024;
-            return lds_cu > 0 && pad + 1024 <= lds_block && blocks * (pad + 1024) <= lds_cu ? pad : 0;
-        };
-        h->lds_pad = pad_for(ags::kCappedBlocksPerCu);
-        h->lds_pad_stats = pad_for(ags::kCappedBlocksPerCuStats);
-        h->lds_pad_update = pad_for(ags::kCappedBlocksPerCuUpdate);
-    }
+    h->shape = ags::launch_shape(*cfg);
+    h->lds_pad = lds_pad_for(dev, h->shape.step_blocks);
+    h->lds_pad_stats = lds_pad_for(dev, h->shape.stats_blocks);
+    h->lds_pad_update = lds_pad_for(dev, h->shape.update_blocks);
     e = hipEventCreateWithFlags(&h->order_ev, hipEventDisableTiming);
     if (e != hipSuccess) {
         h->order_ev = nullptr;
@@ -1324,7 +1327,6 @@ extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w,
     sa.corr = reinterpret_cast<float2*>(ws + wl.corr);
     sa.corr_flag = reinterpret_cast<int*>(nt.counters + 1);
     sa.updated = 0;
-    sa.xcd_map = n_tiles >= ags::kXcdMapMinTiles ? 1 : 0;
     sa.done_count = nt.counters;
     sa.chunks = nt.chunks;
     sa.chunk_sums = reinterpret_cast<ags::ChunkSum*>(ws + wl.chunk_sums);
@@ -1336,6 +1338,8 @@ extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w,
     sa.n_flat = c.n_flat;
     sa.ew_partials = nullptr;
     sa.w_norm_in = nullptr;
+    sa.lds_pad = lds_pad_for(dev, ags::launch_shape(c).stats_blocks);
+    sa.grouped = 1;
 
     e = hipMemcpyAsync(sp, c.layers, (size_t)c.n_layers * sizeof(ags_layer), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {

@@ -40,43 +40,113 @@ constexpr int64_t kMaxTilesPerLayer = AGS_MAX_TILES_PER_LAYER;
 // thread); a layer with more tiles is finalized by several blocks whose sums
 // the last of them combines.
 constexpr int kFinTilesPerChunk = 4096;
-// From this many tiles on, the step kernel gives each XCD a contiguous range
-// of tiles instead of the hardware's round-robin order.  Measured on MI355X
-// (same box, alternating builds): VGG-16, 67,569 tiles, 2.4% faster warm and
-// 2.3% cold with it; ResNet-50, 12,560 tiles, 2.4% slower warm and 4% slower
-// cold (K = 64: 2% and 1.2%); ResNet-18, 5,493 tiles, 4.5% slower.
-constexpr int64_t kXcdMapMinTiles = 32768;
+// Consecutive tiles that one XCD takes at a time (tile_of_block in
+// ags_kernels.hip, which holds the measurements).
+constexpr int kXcdGroup = 8;
 
-// Element scales: the step kernel loads the scales in force and stores the
-// refreshed ones, w and m non-temporally once w, m and the two scale
-// buffers (16 bytes per element) pass this size; below it they can stay in
-// the 256 MB Infinity Cache from one step to the next and ordinary accesses
-// keep them there.  Measured on MI355X, fp32 K = 8, whole step, ordinary
-// against streaming: ResNet-18 (11.2M elements) 113.2 / 113.5 us, 16M
-// elements 157.8 / 157.1, 20M 195.7 / 186.2, ResNet-50 (25.6M) 272.2 /
-// 229.6, VGG-16 (138M) 1400 / 1358.
-constexpr int64_t kEwStreamMinBytes = 192ll << 20;
 // Once w and m (8 bytes per element) pass this size they cannot stay in the
-// Infinity Cache between steps, and every step streams them from HBM with
-// the replicas; the fused step kernel then runs best with two blocks per CU
-// (fewer concurrent streams, so fewer DRAM row conflicts), which the host
-// enforces with an LDS pad.  Measured on MI355X, whole step warm / cold,
-// blocks per CU 5 (the kernel's register limit), 4, 3, 2, 1: VGG-16 K = 8
-// fp32 1210 / 1177, 1187 / 1155, 1176 / 1147, 1164 / 1140, 1378 / 1375 us;
-// the layouts whose w and m fit lose from the cap (ResNet-50 K = 16 bf16
-// 193 -> 201 us, ResNet-18 K = 8 fp32 93 -> 100 us at 2 blocks per CU) or
-// barely gain (ResNet-50 K = 64 bf16 634 -> 631 us).  LARS's two passes on
-// the same layouts: the statistics-only step kernel runs best with three
-// blocks per CU (VGG-16 K = 8 fp32: 936 us uncapped, 901 at 3, 916 at 2),
-// the update kernel with two (525 -> 484 us); the whole LARS step 1471 ->
-// 1381 us.  ResNet-50's first pass loses from a cap (154 -> 160 us at 2).
+// 256 MB Infinity Cache between steps, and every step streams them from HBM
+// with the replicas.
 #ifndef AGS_OCCUPANCY_CAP_MIN_BYTES
 #define AGS_OCCUPANCY_CAP_MIN_BYTES (256ll << 20)
 #endif
 constexpr int64_t kOccupancyCapMinBytes = AGS_OCCUPANCY_CAP_MIN_BYTES;
-constexpr int kCappedBlocksPerCu = 2;
-constexpr int kCappedBlocksPerCuStats = 3;
-constexpr int kCappedBlocksPerCuUpdate = 2;
+
+// How the streaming kernels of a handle (or of a statistics call without
+// one) are launched: the most blocks that share a CU, 0 = as many as the
+// registers allow.
+struct LaunchShape {
+    int step_blocks;    // step kernel with the update
+    int stats_blocks;   // step kernel, statistics only
+    int update_blocks;  // LARS update
+    // Non-temporal (streaming) accesses: to w and m in the step kernel and in
+    // the LARS update, and the stores of the replica mean between them.
+    bool stream_step, stream_update, stream_gbar;
+    bool grouped_step;  // tile order of the step kernel with the update
+};
+
+// The rule behind a LaunchShape.  Fewer resident blocks mean fewer row
+// streams open at once (K + 2 per block), so the DRAM rows are used better,
+// until too few reads are in flight.  Measured on MI355X, kernel alone (us),
+// handles stepping in turn, uncapped / 4 / 3 / 2 blocks per CU:
+//   step, w and m fit the Infinity Cache: ResNet-50 bf16 K = 1 87 / 82 / 84
+//     / 88, K = 4 110 / 107 / 113 / 116, K = 8 144 / 143 / 144 / 145, K = 16
+//     220 / 220 / 220 / 218 (one handle back to back 119 / 117 / 125 / 129
+//     at K = 8: 2 loses); K = 8 fp32 225 / 224 / 223 / 220 -> 4;
+//   step, larger: VGG-16 bf16 K = 1 460 / 425 / 434 / 462, K = 4 575 / 553 /
+//     568 / 602 -> 4; K = 8 791 / 771 / 770 / 754, K = 16 1205 / 1205 / 1202
+//     / 1132, fp32 K = 4 799 / 783 / 774 / 718, K = 8 1224 / 1218 / 1210 /
+//     1155 -> 2 from 16 replica bytes per element on;
+//   element scales, fit: ResNet-50 K = 16 bf16 253 / 254 / 257 / 250, back
+//     to back 215 / 215 / 219 / 226 -> 4; larger: VGG-16 bf16 K = 1 675 /
+//     667 / 617 / 661, K = 4 814 / 816 / 773 / 794 -> 3; K = 16 1425 / 1406
+//     / 1388 / 1293, fp32 K = 4 (streaming) 936 / 933 / 930 / 910 -> 2 from 16
+//     replica bytes per element on;
+//   statistics: VGG-16 bf16 K = 1 122 / 164 / 201 / 277, K = 4 242 / 257 /
+//     301 / 396 -> uncapped below 16 replica bytes per element; K = 8 398 /
+//     386 / 399 / 489, K = 16 687 / 686 / 689 / 739 -> 4; fp32 K = 4 395 /
+//     388 / 378 / 443, K = 8 700 / 694 / 684 / 718 -> 3;
+//   LARS update (and its first pass beside it): ResNet-50 K = 16 bf16 240 / 238 / 241 / 259 -> 4;
+//     larger: VGG-16 K = 8 fp32 1446 / 1420 / 1411 / 1405, bf16 1016 / 998 /
+//     984 / 981 -> 3.
+//   with streaming accesses to w and m, step: VGG-16 fp32 K = 1 464 / 455 /
+//     446 / 455 -> 3 below 16 replica bytes per element; K = 8 1193 / 1174 /
+//     1154 / 1056, ResNet-50 K = 8 fp32 206 / 205 / 203 / 194, ResNet-18
+//     K = 16 fp32 154 / 153 / 150 / 144 -> 2.
+//
+// Streaming accesses to w and m.  Ordinary ones leave the new w and m as
+// dirty lines in the Infinity Cache.  If the next step finds them there (one
+// handle stepping back to back, w and m fit) that saves HBM traffic; if other
+// work evicts them first (a training step's forward and backward passes, or
+// another handle), their write-backs are scattered among the reads of what
+// runs next, and the reads stall on the DRAM's turn-arounds: 204 MB of
+// writes that take 33 us by themselves cost 95 us within a K = 16 step and
+// 170 us within a K = 64 one.  Streaming accesses write straight through but
+// find nothing on the next step.  Both sides measured, kernel alone (us),
+// ordinary -> streaming, handles in turn; back to back:
+//   fit: ResNet-50 bf16 K = 4 107 -> 114; 93 -> 112, K = 8 143 -> 136; 117
+//     -> 134, K = 16 220 -> 205; 177 -> 203 (ordinary); K = 32 373 -> 345;
+//     330 -> 342, K = 64 667 -> 635; 618 -> 634; fp32 K = 4 144 -> 132; 117
+//     -> 133 (ordinary), K = 8 224 -> 194; 180 -> 194; ResNet-18 fp32 K = 8
+//     86 -> 88; 82 -> 87 (ordinary), K = 16 151 -> 144; 145 -> 142;
+//   larger: VGG-16 fp32 K = 1 468 -> 446; 435 -> 446, K = 4 718 -> 684; 694
+//     -> 692, K = 8 1155 -> 1056; 1089 -> 1050; bf16 K = 1 425 -> 447, K = 4
+//     553 -> 607, K = 8 754 -> 749; 726 -> 739 (ordinary), K = 16 1132 ->
+//     1108; 1096 -> 1110;
+//   element scales (w and m loads; the stores always stream): bf16 ResNet-50
+//     K = 16 253 -> 244; 215 -> 243, K = 4 145 -> 157, VGG-16 K = 16 1293 ->
+//     1355 (ordinary); fp32 ResNet-50 K = 8 246 -> 231; 210 -> 230, VGG-16
+//     K = 8 1335 -> 1299; 1334 -> 1277; ResNet-18 K = 16 161 -> 169 (ordinary).
+// LARS's update has just one row (the mean) beside w and m: the whole LARS
+// step ResNet-50 K = 16 bf16 258 -> 238; 232 -> 235, K = 8 180 -> 167; 164
+// -> 166, ResNet-18 K = 8 fp32 112 -> 107; 102 -> 107.  The mean itself
+// streams once it alone outgrows the cache (VGG-16 K = 8 fp32 1365 -> 1312,
+// bf16 986 -> 930; ResNet-50, where it is read back from the cache, 238 ->
+// 243).
+//
+// The grouped tile order (tile_of_block) serves every kernel but the step
+// kernel with element scales of bf16 replicas, whose four fp32 streams
+// outweigh the rows: grouped against dispatch order VGG-16 K = 16 1349 ->
+// 1293, K = 8 973 -> 941, K = 1 638 -> 617, ResNet-50 K = 16 255 -> 253.
+inline LaunchShape launch_shape(const ags_config& c) {
+    const int row = c.K * (c.grad_dtype == AGS_BF16 ? 2 : 4);  // replica bytes per element
+    const bool large = 8 * c.n_flat > kOccupancyCapMinBytes;
+    const bool f32 = c.grad_dtype == AGS_F32;
+    LaunchShape s;
+    s.grouped_step = f32 || !c.elementwise;
+    if (c.elementwise && !f32) s.stream_step = false;
+    else if (large) s.stream_step = f32 || row >= 32;
+    else if (8 * c.n_flat > (128ll << 20)) s.stream_step = row >= (f32 ? 32 : 64);
+    else s.stream_step = 8 * c.n_flat > (32ll << 20) && row >= 64 && !c.elementwise;
+    s.stream_update = 8 * c.n_flat > (64ll << 20);
+    s.stream_gbar = 4 * c.n_flat > kOccupancyCapMinBytes;
+    if (!large) s.step_blocks = s.stream_step && !c.elementwise ? 2 : 4;
+    else if (row >= 16) s.step_blocks = 2;
+    else s.step_blocks = s.stream_step || c.elementwise ? 3 : 4;
+    s.stats_blocks = row < 16 ? 0 : (f32 ? 3 : 4);
+    s.update_blocks = large ? 3 : 4;
+    return s;
+}
 
 // Elements per tile of a layer of numel elements.
 __host__ __device__ inline int64_t tile_elems_for(int64_t numel) {
@@ -162,7 +232,6 @@ struct StepArgs {
     float2* corr;            // [n_layers] correction c = x + y * scale_j (fp32)
     int* corr_flag;          // 1 when some layer needs the correction pass
     int updated;             // the step kernel applied predicted coefficients
-    int xcd_map;             // step kernel: contiguous tile ranges per XCD
     // Step kernel: tiles in reverse order.  Once w and m outgrow the
     // Infinity Cache the host alternates the direction from step to step,
     // so that a step starts on the lines the step before touched last
@@ -179,7 +248,7 @@ struct StepArgs {
     // Element scales (elementwise AGS; all null / 0 otherwise).  The buffer
     // in force and whether a step refreshes are read from the device state
     // (state->ew_cur, state->step), so a captured step replays correctly.
-    int ew;                  // 0: per layer; per element with 1: ordinary, 2: streaming accesses
+    int ew;                  // 0: a scale per layer, 1: per element
     float* ew_buf;           // [2][n_flat] the two scale buffers
     int64_t n_flat;
     float* ew_partials;      // [n_tiles] per-tile sums of the refreshed scales
@@ -187,9 +256,11 @@ struct StepArgs {
     // the statistics-only step kernel takes W from them and skips w.
     const float* w_norm_in;
     // Bytes of dynamic LDS the step kernel is launched with (it uses none):
-    // a pad that caps the blocks resident per CU.  Taken by the fused
-    // per-layer-scale variant and the statistics-only ones.
+    // a pad that caps the blocks resident per CU (launch_shape).
     int lds_pad;
+    int stream_wm;    // streaming accesses to w and m (launch_shape)
+    int stream_gbar;  // streaming stores of the replica mean
+    int grouped;      // grouped tile order (tile_of_block)
 };
 
 struct UpdateArgs {
@@ -214,10 +285,10 @@ struct UpdateArgs {
     // pass sums w^2 (or nullptr).
     float* w_norm_out;
     // Dynamic LDS of the LARS update launch (0: none), a cap on its blocks
-    // per CU.
+    // per CU, and its streaming accesses to w and m (launch_shape).
     int lds_pad;
-    // LARS update: block b takes tile n_tiles - 1 - b (the last tiles
-    // first).  The pass then ends on the first tiles, whose replica mean
+    int stream_wm;
+    // LARS update: the tiles in reverse order (the last tiles first).  The pass then ends on the first tiles, whose replica mean
     // the next statistics pass writes first, and those lines are still in
     // the Infinity Cache: that pass measured 154.4 -> 151.0 us (ResNet-50
     // K = 16 bf16; K = 64 582 -> 574 us) with the update pass unchanged.

@@ -36,8 +36,8 @@ namespace {
 
 // Every byte of a step is touched once, so the replica rows are read with
 // non-temporal (streaming) loads: measured on MI355X, this cuts the step
-// kernel's time by about a quarter against ordinary loads (w and m keep
-// ordinary loads and stores, which measured faster than streaming ones).
+// kernel's time by about a quarter against ordinary loads.  w and m take
+// ordinary or streaming accesses by the rule of launch_shape (ags_internal.h).
 #ifndef AGS_NT_LOADS
 #define AGS_NT_LOADS 1
 #endif
@@ -824,16 +824,19 @@ __device__ __forceinline__ float element_scale(float gsmall, double q, double in
 // the layer is scaled and the step is predicted not sensitive) and, when
 // refresh, the refreshed scales written to gs_new with their sum over the
 // group's elements in sx.  Without EW, per-layer coefficients.
-// EW: 0 = one scale per layer; 1 = element scales, ordinary accesses; 2 =
-// element scales with non-temporal scale loads and scale, w and m stores
-// (the host's choice for working sets the Infinity Cache cannot keep).
+// EW: element scales, with non-temporal scale loads and scale, w and m
+// stores (ordinary ones left the scales, w and m as dirty lines whose later
+// write-backs break up the reads that follow: K = 8 fp32, handles stepping
+// in turn, ResNet-18's 11.2M elements 111 -> 102 us, 6M 60 -> 58 us, equal
+// below; the same handle back to back 96 -> 98, 57 -> 57 us).
+// NTWM: w and m are loaded and stored non-temporally (stream_step).
 // WNC (statistics only): W of the tile comes from the last LARS update
-// pass, so w is not read.  GB (statistics only): store the replica mean
-// for the LARS update pass.  A compile-time choice: testing the pointer at
+// pass, so w is not read.  GB (statistics only): 1 = store the replica mean
+// for the LARS update pass, 2 = the same with streaming stores.  A compile-time choice: testing the pointer at
 // run time had made the K = 16 bf16 statistics kernel keep 183 VGPRs (two
 // waves per SIMD) against 95 with the store unconditional.
-template <typename GT, int KT, int RMODE, bool UPD, int EW, bool FULL, bool WNC = false,
-          bool GB = false>
+template <typename GT, int KT, int RMODE, bool UPD, bool EW, bool NTWM, bool FULL,
+          bool WNC = false, int GB = 0>
 __device__ __forceinline__ void step_group(const StepArgs& a, const GT* __restrict__ g,
                                            int64_t idx, int n0, int n1, int K, float ca,
                                            float cb, float lr, bool use_gs, bool scaled, bool refresh,
@@ -841,32 +844,30 @@ __device__ __forceinline__ void step_group(const StepArgs& a, const GT* __restri
                                            float* __restrict__ gs_new, float smax, float& sw,
                                            float& sg, float& sd, float& ss, float& sx) {
     constexpr int HS = Map<GT>::HS;
-    constexpr bool NT = EW == 2;
-    constexpr bool ELEM = EW != 0;
     static_assert(!(WNC && UPD), "the update reads w");
-    static_assert(!(GB && UPD), "the fused update keeps the mean in registers");
+    static_assert(!(GB != 0 && UPD), "the fused update keeps the mean in registers");
     float wv[kVec], mv[kVec], gb[kVec], dv[kVec], gr[kVec];
     double q[kVec];
-    if (!WNC) load_f32<FULL, HS>(a.w + idx, n0, n1, wv);
-    if (UPD) load_f32<FULL, HS>(a.m + idx, n0, n1, mv);
+    if (!WNC) load_f32_as<NTWM, FULL, HS>(a.w + idx, n0, n1, wv);
+    if (UPD) load_f32_as<NTWM, FULL, HS>(a.m + idx, n0, n1, mv);
     // Keep the w (and m) loads in front of the replica loads: without the
     // barrier the statistics-only variant issued them only after consuming
     // every replica, a second round trip per block.
     if (!UPD && AGS_STATS_WBARRIER) __builtin_amdgcn_sched_barrier(0);
-    constexpr int kb = ELEM ? RawGroup<GT>::kBatchEw : RawGroup<GT>::kBatch;
-    moments<GT, KT, RMODE, FULL, ELEM, kb, !UPD && AGS_STATS_SPLIT>(g, a.stride, idx, n0, n1, K, a.small_replica,
+    constexpr int kb = EW ? RawGroup<GT>::kBatchEw : RawGroup<GT>::kBatch;
+    moments<GT, KT, RMODE, FULL, EW, kb, !UPD && AGS_STATS_SPLIT>(g, a.stride, idx, n0, n1, K, a.small_replica,
                                                a.invK, gb, dv, gr, q);
     float gsv[kVec];
-    if (ELEM) {
+    if (EW) {
         // Old scales: applied on scaled layers, carried over on the others.
         if (use_gs || (refresh && !scaled)) {
-            load_f32_as<NT, FULL, HS>(gs_old + idx, n0, n1, gsv);
+            load_f32_nt<FULL, HS>(gs_old + idx, n0, n1, gsv);
         } else {
 #pragma unroll
             for (int e = 0; e < kVec; ++e) gsv[e] = 1.0f;
         }
     }
-    if (GB) store_f32<FULL, HS>(a.gbar + idx, n0, n1, gb);
+    if (GB) store_f32_as<GB == 2, FULL, HS>(a.gbar + idx, n0, n1, gb);
 #pragma unroll
     for (int e = 0; e < kVec; ++e) {
         if (!WNC) sw = fmaf(wv[e], wv[e], sw);
@@ -880,15 +881,15 @@ __device__ __forceinline__ void step_group(const StepArgs& a, const GT* __restri
         // d = a gbar + b w ; m <- mu m + d ; w <- w - eta m
 #pragma unroll
         for (int e = 0; e < kVec; ++e) {
-            const float ae = (ELEM && use_gs) ? gsv[e] : ca;
+            const float ae = (EW && use_gs) ? gsv[e] : ca;
             const float d = fmaf(ae, gb[e], cb * wv[e]);
             mv[e] = fmaf(a.momentum, mv[e], d);
             wv[e] = fmaf(-lr, mv[e], wv[e]);
         }
-        store_f32_as<NT, FULL, HS>(a.w + idx, n0, n1, wv);
-        store_f32_as<NT, FULL, HS>(a.m + idx, n0, n1, mv);
+        store_f32_as<EW || NTWM, FULL, HS>(a.w + idx, n0, n1, wv);
+        store_f32_as<EW || NTWM, FULL, HS>(a.m + idx, n0, n1, mv);
     }
-    if (ELEM && refresh) {
+    if (EW && refresh) {
         float sn[kVec];
         if (scaled) {
             const double invK = 1.0 / (double)K;
@@ -901,7 +902,7 @@ __device__ __forceinline__ void step_group(const StepArgs& a, const GT* __restri
 #pragma unroll
             for (int e = 0; e < kVec; ++e) sn[e] = gsv[e];
         }
-        store_f32_as<NT, FULL, HS>(gs_new + idx, n0, n1, sn);
+        store_f32_nt<FULL, HS>(gs_new + idx, n0, n1, sn);
 #pragma unroll
         for (int e = 0; e < kVec; ++e) {
             const bool valid = FULL || (e < kHalf ? e < n0 : e - kHalf < n1);
@@ -918,21 +919,33 @@ __device__ __forceinline__ float tree_sum(const float* v) {
     else return tree_sum<N / 2>(v) + tree_sum<N - N / 2>(v + N / 2);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs.  With xcd_map each
-// XCD walks a contiguous range of tiles instead of every 8th tile (a
-// bijection of block indices onto tiles).
-__device__ __forceinline__ int tile_of_block(int b, int n, int xcd_map) {
-    if (!xcd_map) return b;
-    constexpr int nx = 8;
-    const int q = n / nx, r = n % nx, x = b % nx, i = b / nx;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
+// The tile of block b of n.  Workgroups are dispatched round-robin over the
+// 8 XCDs; blocks are taken in runs of 8 * kXcdGroup, and in a run each XCD
+// takes kXcdGroup consecutive tiles (the last, incomplete run keeps the
+// dispatch order).  So an XCD reads 8 tiles' contiguous piece of every row
+// (32 KiB of a bf16 row), and the lines that two neighbouring tiles share
+// once, while the whole chip stays within a window of 64 tiles.  Measured on
+// MI355X, kernel alone, handles stepping in turn, dispatch order / one
+// contiguous range per XCD / this order (us): statistics ResNet-50 K = 16
+// bf16 137 / 133 / 132, K = 64 506 / 478 / 476, VGG-16 K = 8 bf16 425 / 396
+// / 398; step ResNet-50 K = 64 680 / 676 / 667, K = 16 220 / 227 / 220,
+// ResNet-18 K = 8 fp32 89 / 90 / 86, VGG-16 K = 8 fp32 (w and m streamed)
+// 1091 / 1103 / 1056.  Groups of 4 to 128 tiles measure within 2% of 8.
+// Not grouped: the dispatch order (launch_shape's choice for bf16 element
+// scales).
+__device__ __forceinline__ int tile_of_block(int b, int n, int grouped = 1) {
+    constexpr int run = 8 * kXcdGroup;
+    if (!grouped) return b;
+    const int o = b % run;
+    if (b - o + run > n) return b;
+    return b - o + (o % 8) * kXcdGroup + o / 8;
 }
 
-template <typename GT, int KT, int RMODE, bool UPD, int EW, bool WNC = false, bool GB = false>
+template <typename GT, int KT, int RMODE, bool UPD, bool EW, bool NTWM, bool WNC = false,
+          int GB = 0>
 __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
-    constexpr bool ELEM = EW != 0;
     __shared__ float red[5][kTileBlock / 64];
-    const int tb = tile_of_block(blockIdx.x, gridDim.x, a.xcd_map);
+    const int tb = tile_of_block(blockIdx.x, gridDim.x, a.grouped);
     const int ti = a.reverse ? (int)gridDim.x - 1 - tb : tb;
     const Tile t = a.tiles[ti];
     const int l = t.layer;
@@ -954,7 +967,7 @@ __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
                               ? surely_sensitive(a.g_prev_l[l], step) || a.last_sens_l[l] != 0
                               : surely_sensitive(a.state->g_prev, step) || a.state->last_sens != 0;
         scaled = (f & AGS_LAYER_SCALE) != 0;
-        if (ELEM) {
+        if (EW) {
             // The buffer in force and the refresh, from the device state.
             const int cur = a.state->ew_cur;
             gs_old = a.ew_buf + (size_t)cur * (size_t)a.n_flat;
@@ -962,7 +975,7 @@ __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
             refresh = a.refresh_every > 0 && ((step + 1) % a.refresh_every) == 0;
         }
         if (scaled && !pred) {
-            if (ELEM) use_gs = true;
+            if (EW) use_gs = true;
             else if (a.mode == AGS_MODE_AGS) ca = (float)a.gradscale[l];
             else if (a.mode == AGS_MODE_STATIC) ca = (float)a.static_scale;
         }
@@ -972,7 +985,7 @@ __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
 
     float sw = 0.0f, sg = 0.0f, sd = 0.0f, ss = 0.0f, sx = 0.0f;
     for_each_group<Map<GT>::HS>(t.begin, t.count, [&](int64_t idx, int n0, int n1, auto full) {
-        step_group<GT, KT, RMODE, UPD, EW, decltype(full)::value, WNC, GB>(
+        step_group<GT, KT, RMODE, UPD, EW, NTWM, decltype(full)::value, WNC, GB>(
             a, g, idx, n0, n1, K, ca, cb, lr, use_gs, scaled, refresh, gs_old, gs_new, smax, sw, sg,
             sd, ss, sx);
     });
@@ -982,7 +995,7 @@ __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
     sg = wave_sum(sg);
     sd = wave_sum(sd);
     ss = wave_sum(ss);
-    if (ELEM && refresh) sx = wave_sum(sx);
+    if (EW && refresh) sx = wave_sum(sx);
     if (lane == 0) {
         red[0][wid] = sw;
         red[1][wid] = sg;
@@ -998,7 +1011,7 @@ __global__ __launch_bounds__(kTileBlock) void step_kernel(StepArgs a) {
         p.d = tree_sum<kTileBlock / 64>(red[2]);
         p.s = tree_sum<kTileBlock / 64>(red[3]);
         a.partials[ti] = p;
-        if (ELEM && refresh) a.ew_partials[ti] = tree_sum<kTileBlock / 64>(red[4]);
+        if (EW && refresh) a.ew_partials[ti] = tree_sum<kTileBlock / 64>(red[4]);
     }
 }
 
@@ -1113,8 +1126,8 @@ __global__ __launch_bounds__(kTileBlock) void correct_kernel(UpdateArgs a) {
         gs_old = a.ew_buf + (size_t)(refreshed ? 1 - cur : cur) * (size_t)a.n_flat;
     }
 #pragma unroll 1
-    for (int ti = blockIdx.x; ti < a.n_tiles; ti += gridDim.x) {
-        const Tile t = a.tiles[ti];
+    for (int b = blockIdx.x; b < a.n_tiles; b += gridDim.x) {
+        const Tile t = a.tiles[tile_of_block(b, a.n_tiles)];
         const float2 c = a.corr[t.layer];
         if (c.x == 0.0f && c.y == 0.0f) continue;
         if (c.y == 0.0f) {
@@ -1137,13 +1150,14 @@ __global__ __launch_bounds__(kTileBlock) void correct_kernel(UpdateArgs a) {
 // order step_group adds the squares of w (a ragged end's missing elements
 // are 0 on both sides), so that the tile's sum has the bits the next
 // statistics pass would get from reading w.
-template <typename GT, int KT, bool RECOMP, bool FULL, bool WN>
+// NTWM: w and m non-temporally (stream_update).
+template <typename GT, int KT, bool RECOMP, bool FULL, bool WN, bool NTWM>
 __device__ __forceinline__ void update_group(const UpdateArgs& a, const GT* __restrict__ g,
                                              int64_t idx, int n0, int n1, int K, float ca,
                                              float cb, float lr, float& sw) {
     float gb[kVec], wv[kVec], mv[kVec];
-    load_f32<FULL, Map<GT>::HS>(a.w + idx, n0, n1, wv);
-    load_f32<FULL, Map<GT>::HS>(a.m + idx, n0, n1, mv);
+    load_f32_as<NTWM, FULL, Map<GT>::HS>(a.w + idx, n0, n1, wv);
+    load_f32_as<NTWM, FULL, Map<GT>::HS>(a.m + idx, n0, n1, mv);
     if (RECOMP) {
         float dv[kVec], gr[kVec];
         double q[kVec];
@@ -1157,17 +1171,18 @@ __device__ __forceinline__ void update_group(const UpdateArgs& a, const GT* __re
         mv[e] = fmaf(a.momentum, mv[e], d);
         wv[e] = fmaf(-lr, mv[e], wv[e]);
     }
-    store_f32<FULL, Map<GT>::HS>(a.w + idx, n0, n1, wv);
-    store_f32<FULL, Map<GT>::HS>(a.m + idx, n0, n1, mv);
+    store_f32_as<NTWM, FULL, Map<GT>::HS>(a.w + idx, n0, n1, wv);
+    store_f32_as<NTWM, FULL, Map<GT>::HS>(a.m + idx, n0, n1, mv);
     if (WN) {
 #pragma unroll
         for (int e = 0; e < kVec; ++e) sw = fmaf(wv[e], wv[e], sw);
     }
 }
 
-template <typename GT, int KT, bool RECOMP, bool WN>
+template <typename GT, int KT, bool RECOMP, bool WN, bool NTWM>
 __global__ __launch_bounds__(kTileBlock) void update_kernel(UpdateArgs a) {
-    const int ti = a.reverse ? a.n_tiles - 1 - (int)blockIdx.x : (int)blockIdx.x;
+    const int tb = tile_of_block(blockIdx.x, a.n_tiles);
+    const int ti = a.reverse ? a.n_tiles - 1 - tb : tb;
     const Tile t = a.tiles[ti];
     const float2 ab = a.coef[t.layer];
     const GT* __restrict__ g = static_cast<const GT*>(a.grads);
@@ -1175,8 +1190,8 @@ __global__ __launch_bounds__(kTileBlock) void update_kernel(UpdateArgs a) {
     const float lr = a.state->lr;
     float sw = 0.0f;
     for_each_group<Map<GT>::HS>(t.begin, t.count, [&](int64_t idx, int n0, int n1, auto full) {
-        update_group<GT, KT, RECOMP, decltype(full)::value, WN>(a, g, idx, n0, n1, K, ab.x, ab.y,
-                                                                 lr, sw);
+        update_group<GT, KT, RECOMP, decltype(full)::value, WN, NTWM>(a, g, idx, n0, n1, K, ab.x,
+                                                                       ab.y, lr, sw);
     });
     if (WN) {
         // the step kernel's reduction: wave butterfly, then the waves in a
@@ -1216,19 +1231,28 @@ hipError_t launch(void (*k)(A), dim3 grid, dim3 block, hipStream_t s, const A& a
 template <typename GT, int KT, int RMODE>
 hipError_t step_r(const StepArgs& a, int n_tiles, bool update, hipStream_t s, KernelEvents ev) {
     const dim3 grid(n_tiles), block(kTileBlock);
+    const unsigned lds = (unsigned)a.lds_pad;
     if (!update) {
-        const unsigned lds = (unsigned)a.lds_pad;
-        if (a.gbar && a.w_norm_in)
-            return launch(step_kernel<GT, KT, RMODE, false, 0, true, true>, grid, block, s, a, ev, lds);
-        if (a.gbar)
-            return launch(step_kernel<GT, KT, RMODE, false, 0, false, true>, grid, block, s, a, ev, lds);
+        if (a.gbar && a.stream_gbar) {
+            if (a.w_norm_in)
+                return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 2>, grid, block, s, a, ev, lds);
+            return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 2>, grid, block, s, a, ev, lds);
+        }
+        if (a.gbar) {
+            if (a.w_norm_in)
+                return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 1>, grid, block, s, a, ev, lds);
+            return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 1>, grid, block, s, a, ev, lds);
+        }
         if (a.w_norm_in)
-            return launch(step_kernel<GT, KT, RMODE, false, 0, true>, grid, block, s, a, ev, lds);
-        return launch(step_kernel<GT, KT, RMODE, false, 0>, grid, block, s, a, ev, lds);
+            return launch(step_kernel<GT, KT, RMODE, false, false, false, true>, grid, block, s, a, ev, lds);
+        return launch(step_kernel<GT, KT, RMODE, false, false, false>, grid, block, s, a, ev, lds);
     }
-    if (a.ew == 2) return launch(step_kernel<GT, KT, RMODE, true, 2>, grid, block, s, a, ev);
-    if (a.ew) return launch(step_kernel<GT, KT, RMODE, true, 1>, grid, block, s, a, ev);
-    return launch(step_kernel<GT, KT, RMODE, true, 0>, grid, block, s, a, ev, (unsigned)a.lds_pad);
+    if (a.ew) {
+        if (a.stream_wm) return launch(step_kernel<GT, KT, RMODE, true, true, true>, grid, block, s, a, ev, lds);
+        return launch(step_kernel<GT, KT, RMODE, true, true, false>, grid, block, s, a, ev, lds);
+    }
+    if (a.stream_wm) return launch(step_kernel<GT, KT, RMODE, true, false, true>, grid, block, s, a, ev, lds);
+    return launch(step_kernel<GT, KT, RMODE, true, false, false>, grid, block, s, a, ev, lds);
 }
 
 template <typename GT, int KT>
@@ -1243,12 +1267,16 @@ template <typename GT, int KT>
 hipError_t update_k(const UpdateArgs& a, hipStream_t s, KernelEvents ev) {
     const dim3 grid(a.n_tiles), block(kTileBlock);
     const unsigned lds = (unsigned)a.lds_pad;
-    if (a.w_norm_out) {
-        if (a.gbar) return launch(update_kernel<GT, KT, false, true>, grid, block, s, a, ev, lds);
-        return launch(update_kernel<GT, KT, true, true>, grid, block, s, a, ev, lds);
+    if (!a.gbar) {
+        if (a.w_norm_out) return launch(update_kernel<GT, KT, true, true, false>, grid, block, s, a, ev, lds);
+        return launch(update_kernel<GT, KT, true, false, false>, grid, block, s, a, ev, lds);
     }
-    if (a.gbar) return launch(update_kernel<GT, KT, false, false>, grid, block, s, a, ev, lds);
-    return launch(update_kernel<GT, KT, true, false>, grid, block, s, a, ev, lds);
+    if (a.stream_wm) {
+        if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, true>, grid, block, s, a, ev, lds);
+        return launch(update_kernel<GT, KT, false, false, true>, grid, block, s, a, ev, lds);
+    }
+    if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, false>, grid, block, s, a, ev, lds);
+    return launch(update_kernel<GT, KT, false, false, false>, grid, block, s, a, ev, lds);
 }
 
 template <typename GT, int KT>
