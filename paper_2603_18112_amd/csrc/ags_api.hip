@@ -39,7 +39,7 @@ struct WsLayout {
     size_t g_prev_l = 0;                  // [L] fp64 per-layer G_prev
     size_t last_sens_l = 0;               // [L] int32 per-layer last sensitive bit
     size_t chunks = 0, chunk_sums = 0, chunk_count = 0;
-    size_t counters_bytes = 0;  // finished-layer counter, correction flag
+    size_t counters_bytes = 0;  // finished-layer counter, correction count
     size_t lstats = 0, gstats = 0, gradscale = 0, state = 0, end = 0;
     size_t rec_bytes = 0;    // lstats .. gstats end
     size_t state_bytes = 0;  // gradscale .. state end
@@ -361,7 +361,10 @@ struct ags_handle {
         return cfg.elementwise ? reinterpret_cast<float*>(ws + wl.ew_partials) : nullptr;
     }
     unsigned* done_count() const { return reinterpret_cast<unsigned*>(ws + wl.counters); }
-    int* corr_flag() const { return reinterpret_cast<int*>(done_count() + 1); }
+    int* corr_count() const { return reinterpret_cast<int*>(done_count() + 1); }
+    // The correction list takes the place of LARS's coefficients (a handle
+    // has one or the other).
+    int* corr_list() const { return reinterpret_cast<int*>(ws + wl.coef); }
     float* gbar() const { return materialize ? reinterpret_cast<float*>(ws + wl.gbar) : nullptr; }
     float* w_norm() const { return cfg.reuse_w_norms ? reinterpret_cast<float*>(ws + wl.w_norm) : nullptr; }
     ags_layer_stats* lstats() const { return reinterpret_cast<ags_layer_stats*>(ws + wl.lstats); }
@@ -514,7 +517,8 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
     sa.delta_scope = c.delta_scope;
     sa.coef = h->coef();
     sa.corr = h->corr();
-    sa.corr_flag = h->corr_flag();
+    sa.corr_list = h->corr_list();
+    sa.corr_count = h->corr_count();
     sa.updated = fused ? 1 : 0;
     // A captured step keeps the forward direction (its replays cannot
     // alternate); the results are the same either way, only the order of
@@ -560,7 +564,9 @@ ags_status launch_step(ags_handle* h, const void* d_grads, int64_t stride, hipSt
         ua.n_flat = c.n_flat;
         ua.state = h->state();
         ua.refresh_every = c.refresh_every;
-        ua.corr_flag = h->corr_flag();
+        ua.corr_list = h->corr_list();
+        ua.corr_count = h->corr_count();
+        ua.layers = h->ldev();
         ua.momentum = (float)c.momentum;
         ua.w_norm_out = (c.mode == AGS_MODE_LARS) ? h->w_norm() : nullptr;
         ua.lds_pad = h->lds_pad_update;
@@ -1110,7 +1116,7 @@ struct NoallocTables {
     double* g_prev_l;
     int32_t* last_sens_l;
     unsigned* chunk_count;
-    unsigned* counters;  // finished-layer counter, correction flag
+    unsigned* counters;  // finished-layer counter, correction count
 };
 
 // One block: every layer's tile and chunk ranges (an exclusive scan of the
@@ -1325,7 +1331,8 @@ extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w,
     sa.delta_scope = c.delta_scope;
     sa.coef = reinterpret_cast<float2*>(ws + wl.coef);
     sa.corr = reinterpret_cast<float2*>(ws + wl.corr);
-    sa.corr_flag = reinterpret_cast<int*>(nt.counters + 1);
+    sa.corr_list = reinterpret_cast<int*>(ws + wl.coef);
+    sa.corr_count = reinterpret_cast<int*>(nt.counters + 1);
     sa.updated = 0;
     sa.done_count = nt.counters;
     sa.chunks = nt.chunks;

@@ -157,8 +157,8 @@ __host__ __device__ inline int64_t tile_elems_for(int64_t numel) {
 #ifndef AGS_CORRECT_BLOCKS
 #define AGS_CORRECT_BLOCKS 512
 #endif
-// Grid of the correction pass (grid-stride over tiles): small, because on
-// most steps the pass only reads its flag and exits.
+// Grid of the correction pass: small, because on most steps the pass only
+// reads its list's length and exits.
 constexpr int kCorrectBlocks = AGS_CORRECT_BLOCKS;
 
 struct Tile {
@@ -184,7 +184,7 @@ struct ChunkSum {
     double w, g, d, s, x;  // x: sum of the refreshed element scales
 };
 
-// Device-resident AGS state, updated by the last block of a committed step.
+// Device-resident AGS state, updated by the last finalize block of a committed step.
 struct DevState {
     double g_prev;      // ||G||^2 of the last committed step (0 before the first)
     int64_t step;       // steps completed
@@ -228,9 +228,10 @@ struct StepArgs {
     double* g_prev_l;        // [n_layers] G_l of the last committed step
     int32_t* last_sens_l;    // [n_layers] the bit that decided each layer then
     int delta_scope;         // ags_delta_scope
-    float2* coef;            // [n_layers] (a_l, b_l) as applied, fp32
-    float2* corr;            // [n_layers] correction c = x + y * scale_j (fp32)
-    int* corr_flag;          // 1 when some layer needs the correction pass
+    float2* coef;            // [n_layers] LARS: (a_l, b_l), fp32
+    float2* corr;            // [n_layers] correction c = x + y * scale_j (fp32) of listed layers
+    int* corr_list;          // [n_layers] the layers that need the correction pass
+    int* corr_count;         // how many
     int updated;             // the step kernel applied predicted coefficients
     // Step kernel: tiles in reverse order.  Once w and m outgrow the
     // Infinity Cache the host alternates the direction from step to step,
@@ -274,12 +275,14 @@ struct UpdateArgs {
     float* w;
     float* m;
     const float2* coef;   // LARS update: (a_l, b_l)
-    const float2* corr;   // correction pass: c = x + y * gs_old_j per layer
+    const LayerDev* layers;  // correction pass: the listed layers' tiles
+    const float2* corr;   // correction pass: c = x + y * gs_old_j of a listed layer
+    const int* corr_list;
+    const int* corr_count;
     const float* ew_buf;  // [2][n_flat] element scales (or null)
     int64_t n_flat;
     const DevState* state;  // after the step: the buffer in force and the step count
     int refresh_every;
-    const int* corr_flag;
     float momentum;          // lr: state->lr
     // LARS update: per-tile sums of the new w^2, summed as the statistics
     // pass sums w^2 (or nullptr).

@@ -172,3 +172,28 @@ def test_layer_state_argument_errors():
     g, per = p.gpu.get_last_decision()
     assert g == 0 and list(per) == [1, 0]
     p.close()
+
+
+@pytest.mark.parametrize("n_layers,big", [(1, 0), (255, 0), (257, 0), (1023, 0), (1025, 0),
+                                          (1400, 0), (3, 4096 * 2048), (3, 4096 * 2048 + 1)])
+def test_correction_list_and_layer_records_at_their_edges(n_layers, big):
+    """Layer counts around the rounds of 256 in which the last finalize block
+    takes the layers' records (four rounds kept, later ones loaded again) and
+    the correction pass its list, and a layer of exactly and just over one
+    finalize chunk: two layers of three change their norms on step 2, every
+    layer on step 3, none on step 4."""
+    sizes = [1 + (7 * l) % 40 for l in range(n_layers)]
+    if big:
+        sizes[1] = big
+    lay = layouts.custom_layout(sizes, pad=8)
+    K = 2
+    table = lay.table()
+    base = synth.replica_grads(lay, K, 0, 11, dtype="f32")
+    L = len(table)
+    f2 = [1.0 if l % 3 == 0 else 2.0 for l in range(L)]
+    f3 = [0.25 * f for f in f2]
+    p = Pair(lay, K, seed=11, delta_scope="layer")
+    for t, f in enumerate([[1.0] * L, f2, f3, f3], 1):
+        p.step(_rescale(base, table, f), what=f"{n_layers} layers, step {t}")
+        p.check_state(f"{n_layers} layers, step {t}")
+    p.close()
