@@ -286,19 +286,23 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                                         float (&gbar)[kVec], float (&dev)[kVec],
                                         float (&gr)[kVec], double (&q)[kVec]) {
     float g0[kVec], s1[kVec], s2[kVec];
-    if (FULL) {
+    auto shift = [&]() {  // replica 0 is in g0
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) {
+            s1[e] = 0.0f;
+            s2[e] = 0.0f;
+            gr[e] = g0[e];
+            if (EX) q[e] = (double)g0[e];
+        }
+    };
+    if constexpr (FULL && KT > 0) {
         RawGroup<GT> r0;
         r0.load(g + idx);
         r0.widen(g0);
-    } else {
+        shift();
+    } else if constexpr (!FULL) {
         load_tail<GT, Map<GT>::HS>(g + idx, n0, n1, g0);
-    }
-#pragma unroll
-    for (int e = 0; e < kVec; ++e) {
-        s1[e] = 0.0f;
-        s2[e] = 0.0f;
-        gr[e] = g0[e];
-        if (EX) q[e] = (double)g0[e];
+        shift();
     }
     auto acc = [&](int k, const float (&x)[kVec]) {
 #pragma unroll
@@ -425,36 +429,71 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
             }
         };
         int k = 1;
-#pragma unroll 1
-        for (; k + 3 < K; k += 4) {
-            float x[4][kVec];
+        if constexpr (FULL) {
+            // Replica 0 and the 1 to 4 replicas left over beside whole fours
+            // in one round trip, then eights (bf16) and fours.  (Replica 0,
+            // the fours and each replica left over had a round trip of their
+            // own, six for K = 12 instead of two: ResNet-50 K = 12 bf16
+            // step 203 -> 190 us, K = 3 bf16 VGG-16's three round trips are
+            // now one.  fp32 eights would hold 64 registers of loads.)
+            auto sum = [&](const auto& x, int k0, auto from, auto to) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (FULL) {
-                    RawGroup<GT> q;
-                    q.load(g + (int64_t)(k + j) * stride + idx);
-                    q.widen(x[j]);
-                } else {
-                    load_tail<GT, Map<GT>::HS>(g + (int64_t)(k + j) * stride + idx, n0, n1, x[j]);
+                for (int j = decltype(from)::value; j < decltype(to)::value; ++j) {
+                    float v[kVec];
+                    x[j].widen(v);
+                    acc(k0 + j, v);
+                }
+                flush();
+            };
+            using C0 = std::integral_constant<int, 0>;
+            using C4 = std::integral_constant<int, 4>;
+            using C8 = std::integral_constant<int, 8>;
+            auto head = [&](auto n) {
+                RawGroup<GT> r0, x[decltype(n)::value];
+                r0.load(g + idx);
+#pragma unroll
+                for (int j = 0; j < decltype(n)::value; ++j)
+                    x[j].load(g + (int64_t)(1 + j) * stride + idx);
+                r0.widen(g0);
+                shift();
+                sum(x, 1, C0{}, n);
+            };
+            const int left = ((K - 2) & 3) + 1;  // K >= 3 here
+            if (left == 1) head(std::integral_constant<int, 1>{});
+            else if (left == 2) head(std::integral_constant<int, 2>{});
+            else if (left == 3) head(std::integral_constant<int, 3>{});
+            else head(C4{});
+            k += left;
+            if constexpr (sizeof(GT) == 2) {
+#pragma unroll 1
+                for (; k + 7 < K; k += 8) {
+                    RawGroup<GT> x[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[j].load(g + (int64_t)(k + j) * stride + idx);
+                    sum(x, k, C0{}, C4{});
+                    sum(x, k, C4{}, C8{});
                 }
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc(k + j, x[j]);
-            flush();
-        }
 #pragma unroll 1
-        for (; k < K; ++k) {
-            float x[kVec];
-            if (FULL) {
-                RawGroup<GT> q;
-                q.load(g + (int64_t)k * stride + idx);
-                q.widen(x);
-            } else {
-                load_tail<GT, Map<GT>::HS>(g + (int64_t)k * stride + idx, n0, n1, x);
+            for (; k + 3 < K; k += 4) {
+                RawGroup<GT> x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j].load(g + (int64_t)(k + j) * stride + idx);
+                sum(x, k, C0{}, C4{});
             }
-            acc(k, x);
+        } else {
+            // the ragged end (one group of a layer at most)
+#pragma unroll 1
+            for (; k < K; k += 4) {
+#pragma unroll 1
+                for (int j = k; j < min(k + 4, K); ++j) {
+                    float x[kVec];
+                    load_tail<GT, Map<GT>::HS>(g + (int64_t)j * stride + idx, n0, n1, x);
+                    acc(j, x);
+                }
+                flush();
+            }
         }
-        flush();
         const double dK = (double)K;
 #pragma unroll
         for (int e = 0; e < kVec; ++e) {

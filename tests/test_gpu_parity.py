@@ -977,3 +977,16 @@ def test_matches_golden_oracle_fixture():
             scale = np.maximum(np.abs(ref), np.sqrt(np.mean(ref * ref)))
             assert np.all(np.abs(got - ref) <= PARAM_RTOL * scale)
     h.close()
+
+
+@pytest.mark.parametrize("K", [3, 5, 6, 7, 9, 11, 13, 14, 15, 17, 18, 21])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_replica_counts_around_the_batches(K, dtype):
+    """Replica counts without a kernel of their own: 1 to 4 replicas beside
+    replica 0, then none, one or several batches of eight and of four; layers
+    with whole groups and ragged ends, every small-batch choice."""
+    lay = layouts.custom_layout([4096, 2049, 2047, 77, 8, 1], pad=8)
+    for r in (0, -1, K - 1):
+        run_steps(lay, K, 2, dtype=dtype, small_replica=r, seed=K, label=f"K={K} {dtype} r={r}")
+    run_steps(lay, K, 2, dtype=dtype, mode="ags", elementwise=True, seed=K,
+              label=f"K={K} {dtype} element scales")
