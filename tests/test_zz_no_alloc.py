@@ -125,3 +125,29 @@ def test_noalloc_random_configs_match_ags_stats():
                     scaled=[bool(f & layouts.LAYER_SCALE) for _, _, f in lay.table()])
         assert torch.equal(w, torch.from_numpy(w0).cuda()), what
         del g, w, m
+
+
+@pytest.mark.parametrize("n_layers", [1, 511, 512, 513, 1025])
+def test_noalloc_tables_with_layers_sharing_blocks(n_layers):
+    """Layer counts around the 512 blocks that build the tables (then several
+    layers share a block, and the last blocks may have none), layers of one to
+    three tiles: bitwise equal to a handle's ags_stats."""
+    import torch
+    sizes = [1 + (1237 * l) % 4300 for l in range(n_layers)]
+    lay = layouts.custom_layout(sizes, pad=8)
+    K = 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_layers)
+    w = torch.randn(lay.n_flat, device="cuda", generator=gen)
+    g = torch.randn(K, lay.n_flat, device="cuda", generator=gen)
+    m = torch.zeros_like(w)
+    cfg = ags.make_config(lay.table(), lay.n_flat, K)
+    nl, ng = ags.ags_stats_noalloc(cfg, w.data_ptr(), g.data_ptr(), lay.n_flat,
+                                   torch.cuda.current_stream().cuda_stream)
+    h = ags.AGS(lay.table(), w, m, K)
+    h.stats(g)
+    s = h.read_stats()
+    h.close()
+    for f in ags.LAYER_STATS_FIELDS:
+        assert np.array_equal(nl[f], s.layer[f]), (n_layers, f)
+    assert ng == s.glob
