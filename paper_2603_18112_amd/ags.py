@@ -70,6 +70,8 @@ class ags_global_stats(ctypes.Structure):
 
 
 LAYER_STATS_FIELDS = tuple(n for n, _ in ags_layer_stats._fields_ if n != "reserved")
+#: the same record as numpy sees it
+_LAYER_RECORD = np.dtype(ags_layer_stats)
 #: every function the header declares
 EXPORTS = ("ags_workspace_bytes", "ags_init", "ags_stats", "ags_step", "ags_read_stats",
            "ags_set_lr", "ags_get_state", "ags_set_state", "ags_get_layer_state",
@@ -201,14 +203,24 @@ def ags_step(handle, d_grads: int, replica_stride: int, stream: int = 0):
     _check(load_library().ags_step(handle, d_grads, int(replica_stride), stream), handle)
 
 
-def ags_read_stats(handle, n_layers: int):
-    arr = (ags_layer_stats * max(n_layers, 1))()
-    g = ags_global_stats()
-    _check(load_library().ags_read_stats(handle, ctypes.cast(arr, ctypes.c_void_p), ctypes.byref(g)), handle)
-    layer = {f: np.array([getattr(arr[i], f) for i in range(n_layers)]) for f in LAYER_STATS_FIELDS}
+def _records(rec, n_layers, g):
+    """The records as (per-layer dict of arrays, global dict).  A field is
+    one strided copy: a Python loop over layers and fields took 220 us of a
+    call with 300 layers, five times what the device took."""
+    layer = {}
+    for f in LAYER_STATS_FIELDS:
+        a = rec[f][:n_layers]
+        layer[f] = a.astype(np.int64 if a.dtype.kind == "i" else np.float64)
     glob = {"step": int(g.step), "g_sq": g.g_sq, "g_sq_prev": g.g_sq_prev, "delta": g.delta,
             "sensitive": int(g.sensitive), "nonfinite": int(g.nonfinite)}
     return layer, glob
+
+
+def ags_read_stats(handle, n_layers: int):
+    rec = np.zeros(max(n_layers, 1), _LAYER_RECORD)
+    g = ags_global_stats()
+    _check(load_library().ags_read_stats(handle, rec.ctypes.data, ctypes.byref(g)), handle)
+    return _records(rec, n_layers, g)
 
 
 def ags_set_lr(handle, lr: float):
@@ -236,15 +248,11 @@ def ags_stats_noalloc(cfg, d_w: int, d_grads: int, replica_stride: int, stream: 
     """Statistics of one replica set without a handle and without any device
     allocation; returns (per-layer dict, global dict) like ags_read_stats."""
     n = int(cfg.n_layers)
-    arr = (ags_layer_stats * max(n, 1))()
+    rec = np.zeros(max(n, 1), _LAYER_RECORD)
     g = ags_global_stats()
     _check(load_library().ags_stats_noalloc(ctypes.byref(cfg), d_w, d_grads, int(replica_stride),
-                                            ctypes.cast(arr, ctypes.c_void_p), ctypes.byref(g),
-                                            stream))
-    layer = {f: np.array([getattr(arr[i], f) for i in range(n)]) for f in LAYER_STATS_FIELDS}
-    glob = {"step": int(g.step), "g_sq": g.g_sq, "g_sq_prev": g.g_sq_prev, "delta": g.delta,
-            "sensitive": int(g.sensitive), "nonfinite": int(g.nonfinite)}
-    return layer, glob
+                                            rec.ctypes.data, ctypes.byref(g), stream))
+    return _records(rec, n, g)
 
 
 def ags_invalidate_weight_norms(handle):
