@@ -637,7 +637,7 @@ __device__ Sum4 sum_tiles(const StepArgs& a, int tb, int te, Sum4* sh, bool ew_r
 // write back and invalidate the L2, everything left to the last block, the
 // kernel took (MI355X, before -> now): 161 layers of ResNet-50 10.4 -> 8.8
 // us, 62 of ResNet-18 8.2 -> 6.9, 300 of a generic model 14.7 -> 9.3, VGG-16
-// (a layer of 13 chunks) -> 11.2; a kernel that does nothing takes 4.5 there.
+// (a layer of 13 chunks) 13.9 -> 11.3; a kernel that does nothing takes 4.5 there.
 // All of a thread's tile partials loaded in one go measured the same.
 //
 // Delta = |G - G_prev| / G_prev, infinite on a first step, when G_prev <= 0
