@@ -429,6 +429,7 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
             }
         };
         int k = 1;
+        const int left = ((K - 2) & 3) + 1;  // K >= 3 here
         if constexpr (FULL) {
             // Replica 0 and the 1 to 4 replicas left over beside whole fours
             // in one round trip, then eights (bf16) and fours.  (Replica 0,
@@ -458,7 +459,6 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 shift();
                 sum(x, 1, C0{}, n);
             };
-            const int left = ((K - 2) & 3) + 1;  // K >= 3 here
             if (left == 1) head(std::integral_constant<int, 1>{});
             else if (left == 2) head(std::integral_constant<int, 2>{});
             else if (left == 3) head(std::integral_constant<int, 3>{});
@@ -482,16 +482,20 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 sum(x, k, C0{}, C4{});
             }
         } else {
-            // the ragged end (one group of a layer at most)
+            // The ragged end (one group of a layer at most), in the full
+            // groups' batches: an element's mean has the same bits wherever
+            // its layer ends.
+            int end = k + left;
 #pragma unroll 1
-            for (; k < K; k += 4) {
+            while (k < K) {
 #pragma unroll 1
-                for (int j = k; j < min(k + 4, K); ++j) {
+                for (; k < end; ++k) {
                     float x[kVec];
-                    load_tail<GT, Map<GT>::HS>(g + (int64_t)j * stride + idx, n0, n1, x);
-                    acc(j, x);
+                    load_tail<GT, Map<GT>::HS>(g + (int64_t)k * stride + idx, n0, n1, x);
+                    acc(k, x);
                 }
                 flush();
+                end += 4;
             }
         }
         const double dK = (double)K;

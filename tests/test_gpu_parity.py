@@ -990,3 +990,31 @@ def test_replica_counts_around_the_batches(K, dtype):
         run_steps(lay, K, 2, dtype=dtype, small_replica=r, seed=K, label=f"K={K} {dtype} r={r}")
     run_steps(lay, K, 2, dtype=dtype, mode="ags", elementwise=True, seed=K,
               label=f"K={K} {dtype} element scales")
+
+
+@pytest.mark.parametrize("K", [3, 5, 6, 7, 8, 12, 18, 21])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("elementwise", [False, True])
+def test_an_elements_update_does_not_depend_on_where_its_layer_ends(K, dtype, elementwise):
+    """Layers of 2048 elements (whole groups only) and the same layers one
+    element shorter (a ragged group of 7 elements each): the elements both
+    have take the same update, bit for bit.  Unscaled layers and no decay, so
+    that the update is the replica mean's alone."""
+    import torch
+    n = 192
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    g = torch.randn(K, n * 2048, device="cuda", generator=gen)
+    if dtype == "bf16":
+        g = g.to(torch.bfloat16)
+    out = []
+    for size in (2048, 2047):
+        table = [(2048 * l, size, 0) for l in range(n)]
+        w = torch.zeros(n * 2048, device="cuda")
+        m = torch.zeros_like(w)
+        h = ags.AGS(table, w, m, K, grad_dtype=dtype, elementwise=elementwise)
+        h.step(g)
+        torch.cuda.synchronize()
+        h.close()
+        out.append((w.view(n, 2048)[:, :2047], m.view(n, 2048)[:, :2047]))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
