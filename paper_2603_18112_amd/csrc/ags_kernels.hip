@@ -672,13 +672,24 @@ __device__ __forceinline__ T agent_load(const T* p) {
     return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Counts this thread's block in and returns the count before it.  The wait
-// comes first: the thread's earlier agent-scope stores have then reached the
-// level that every XCD reads them from.  (A release fence would also write
-// back the L2, which holds nothing that another block of the launch reads.)
+// Counts this thread's block in and returns the count before it.  What the
+// thread stored before it with agent_store is visible to what a thread that
+// sees the count loads after it with agent_load.  The memory model would ask
+// for release and acquire fences, which write back and invalidate the XCD's
+// L2, though it holds nothing that another block of the launch reads; the
+// order here rests on gfx950 instead.  Stores before: agent-scope stores
+// write through, and vmcnt reaches 0 once they have reached the level that
+// every XCD reads them from.  Loads after: they are issued in program order
+// behind a branch on the count, which waits for the atomic's reply, and go
+// past the XCD's L2; the second asm keeps the compiler from moving them up.
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "the order that count_in relies on is argued for gfx950 only"
+#endif
 __device__ __forceinline__ unsigned count_in(unsigned* p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned before = __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    return before;
 }
 
 enum : unsigned {
