@@ -65,34 +65,50 @@ struct LaunchShape {
     bool grouped_step;  // tile order of the step kernel with the update
 };
 
-// The rule behind a LaunchShape.  Fewer resident blocks mean fewer row
-// streams open at once (K + 2 per block), so the DRAM rows are used better,
-// until too few reads are in flight.  Measured on MI355X, kernel alone (us),
-// handles stepping in turn, uncapped / 4 / 3 / 2 blocks per CU:
-//   step, w and m fit the Infinity Cache: ResNet-50 bf16 K = 1 87 / 82 / 84
-//     / 88, K = 4 110 / 107 / 113 / 116, K = 8 144 / 143 / 144 / 145, K = 16
-//     220 / 220 / 220 / 218 (one handle back to back 119 / 117 / 125 / 129
-//     at K = 8: 2 loses); K = 8 fp32 225 / 224 / 223 / 220 -> 4;
-//   step, larger: VGG-16 bf16 K = 1 460 / 425 / 434 / 462, K = 4 575 / 553 /
-//     568 / 602 -> 4; K = 8 791 / 771 / 770 / 754, K = 16 1205 / 1205 / 1202
-//     / 1132, fp32 K = 4 799 / 783 / 774 / 718, K = 8 1224 / 1218 / 1210 /
-//     1155 -> 2 from 16 replica bytes per element on;
-//   element scales, fit: ResNet-50 K = 16 bf16 253 / 254 / 257 / 250, back
-//     to back 215 / 215 / 219 / 226 -> 4; larger: VGG-16 bf16 K = 1 675 /
-//     667 / 617 / 661, K = 4 814 / 816 / 773 / 794 -> 3; K = 16 1425 / 1406
-//     / 1388 / 1293, fp32 K = 4 (streaming) 936 / 933 / 930 / 910 -> 2 from 16
-//     replica bytes per element on;
-//   statistics: VGG-16 bf16 K = 1 122 / 164 / 201 / 277, K = 4 242 / 257 /
-//     301 / 396 -> uncapped below 16 replica bytes per element; K = 8 398 /
-//     386 / 399 / 489, K = 16 687 / 686 / 689 / 739 -> 4; fp32 K = 4 395 /
-//     388 / 378 / 443, K = 8 700 / 694 / 684 / 718 -> 3;
-//   LARS update (and its first pass beside it): ResNet-50 K = 16 bf16 240 / 238 / 241 / 259 -> 4;
-//     larger: VGG-16 K = 8 fp32 1446 / 1420 / 1411 / 1405, bf16 1016 / 998 /
-//     984 / 981 -> 3.
-//   with streaming accesses to w and m, step: VGG-16 fp32 K = 1 464 / 455 /
-//     446 / 455 -> 3 below 16 replica bytes per element; K = 8 1193 / 1174 /
-//     1154 / 1056, ResNet-50 K = 8 fp32 206 / 205 / 203 / 194, ResNet-18
-//     K = 16 fp32 154 / 153 / 150 / 144 -> 2.
+// The rule behind a LaunchShape, by the bytes of w and m together ("size"
+// below), the replica bytes per element ("row"), type and kernel.  All
+// figures are whole calls on MI355X in us: three handles in turn; one handle
+// back to back; one step after a 1 GiB read that evicts the caches.  Layouts
+// without a name are layers of 2048 to 2.4 million elements.
+//
+// Blocks per CU.  Fewer resident blocks mean fewer row streams open at once
+// (K + 2 per block), so the DRAM rows are used better, until too few reads
+// are in flight; small layouts, whose blocks the chip holds at once, only
+// lose.
+//   Step kernel, ordinary accesses, w and m fit: 4 from 40 MiB on against no
+//     cap (bf16 K = 1 32 MiB 24.5 -> 24.9; 23.0 -> 23.1; 28.0 -> 28.0, fp32 K
+//     = 4 32 MiB 30.4 -> 30.9; 30.1 -> 30.4; 34.3 -> 34.6, bf16 K = 1 48 MiB
+//     31.7 -> 30.6; 30.7 -> 30.0; 35.1 -> 33.6, 195 MiB 96 -> 92; 84 -> 82;
+//     86 -> 83, bf16 K = 8 156 -> 152; 128 -> 125; 143 -> 141, K = 16 and
+//     fp32 within 1%); element scales: no cap (4 measures the same at every
+//     size, fp32 K = 8 and bf16 K = 16).
+//   Ordinary accesses, larger: row < 16 4 (bf16 K = 4 1056 MiB 573 -> 606 at
+//     2), else 2 against 4 (fp32 K = 4 280 MiB 216 -> 206; 175 -> 182; 187 ->
+//     194, 450 MiB 348 -> 322; 298 -> 302; 306 -> 311, bf16 K = 8 1056 MiB 768
+//     -> 755; 739 -> 729; 733 -> 741, K = 16 1254 -> 1179; 1152 -> 1144; 1179
+//     -> 1171).  Element scales: row < 16 3 against 4 (fp32 K = 1 600 MiB 405
+//     -> 380; 353 -> 343; 363 -> 351, bf16 K = 4 473 -> 456; 432 -> 424; 439
+//     -> 428); else 2 against 3 for bf16 (K = 16 280 MiB 389 -> 378; 339 ->
+//     350; 364 -> 366, 1056 MiB 1431 -> 1349; 1372 -> 1328; 1384 -> 1343), for
+//     fp32 from 512 MiB on (K = 4 450 MiB 420 -> 413; 370 -> 392; 380 -> 398,
+//     600 MiB 563 -> 541; 509 -> 519; 520 -> 529, 1056 MiB 1011 -> 940; 935 ->
+//     911; 945 -> 918; K = 8 the same either way).
+//   Streaming accesses: row < 16 3 against 2 (fp32 K = 1 280 MiB 125 / 130;
+//     125 / 131; 129 / 138), else 2 against 3 (fp32 K = 8 280 MiB 302 -> 287;
+//     303 -> 286; 303 -> 291, K = 16 element scales 195 MiB 403 -> 388; 400 ->
+//     383; 406 -> 387, bf16 K = 16 and 32 the same) or none (K = 16 fp32 24
+//     MiB 51 -> 49; 50 -> 48; 55 -> 52, 85 MiB 163 -> 154; 161 -> 153; 167 ->
+//     156).
+//   Statistics (alone, handles in turn; no cap / 4 / 3): row < 16 none (bf16
+//     K = 1 195 MiB 31 / 40 / 47); else from 64 MiB on 3 for fp32 (K = 8 16
+//     MiB 19.7 / 19.7 / 20.8, 64 MiB 53.0 / 52.1 / 52.6, 85 MiB 67.4 / 66.6 /
+//     66.4, 1056 MiB 718 / 700 / 689; LARS's whole step 64 MiB 84.9 -> 86.0 at
+//     3, 85 MiB 108.2 -> 108.2, 195 MiB 238 -> 234) and 4 for bf16 (K = 8 64 MiB 34.1 / 34.9 / 36.8, 450 MiB
+//     184 / 180 / 187; K >= 16 the same).
+//   LARS update (whole step): from 64 MiB on 4 (K = 16 bf16 195 MiB 256 -> 252;
+//     250 -> 247; 256 -> 252, below the same), larger 3 (K = 8 fp32 400 MiB
+//     483 -> 482; 480 -> 479; 486 -> 482, 1056 MiB 1297 -> 1275; 1312 -> 1289;
+//     1321 -> 1280).
 //
 // Streaming accesses to w and m.  Ordinary ones leave the new w and m as
 // dirty lines in the Infinity Cache.  If the next step finds them there (one
@@ -126,25 +142,29 @@ struct LaunchShape {
 //
 // The grouped tile order (tile_of_block) serves every kernel but the step
 // kernel with element scales of bf16 replicas, whose four fp32 streams
-// outweigh the rows: grouped against dispatch order VGG-16 K = 16 1349 ->
-// 1293, K = 8 973 -> 941, K = 1 638 -> 617, ResNet-50 K = 16 255 -> 253.
+// outweigh the rows: grouped against dispatch order (kernel alone, in turn)
+// VGG-16 K = 16 1349 -> 1293, K = 8 973 -> 941, K = 1 638 -> 617, ResNet-50
+// K = 16 255 -> 253.
 inline LaunchShape launch_shape(const ags_config& c) {
     const int row = c.K * (c.grad_dtype == AGS_BF16 ? 2 : 4);  // replica bytes per element
-    const bool large = 8 * c.n_flat > kOccupancyCapMinBytes;
-    const bool f32 = c.grad_dtype == AGS_F32;
+    const int64_t size = 8 * c.n_flat;                         // bytes of w and m
+    const bool large = size > kOccupancyCapMinBytes, larger = size > 2 * kOccupancyCapMinBytes;
+    const bool f32 = c.grad_dtype == AGS_F32, ew = c.elementwise != 0;
+    constexpr int64_t MiB = 1 << 20;
     LaunchShape s;
-    s.grouped_step = f32 || !c.elementwise;
-    if (c.elementwise && !f32) s.stream_step = false;
+    s.grouped_step = f32 || !ew;
+    if (ew && !f32) s.stream_step = false;
     else if (large) s.stream_step = f32 || row >= 32;
-    else if (8 * c.n_flat > (128ll << 20)) s.stream_step = row >= (f32 ? 32 : 64);
-    else s.stream_step = 8 * c.n_flat > (32ll << 20) && row >= 64 && !c.elementwise;
-    s.stream_update = 8 * c.n_flat > (64ll << 20);
-    s.stream_gbar = 4 * c.n_flat > kOccupancyCapMinBytes;
-    if (!large) s.step_blocks = s.stream_step && !c.elementwise ? 2 : 4;
-    else if (row >= 16) s.step_blocks = 2;
-    else s.step_blocks = s.stream_step || c.elementwise ? 3 : 4;
-    s.stats_blocks = row < 16 ? 0 : (f32 ? 3 : 4);
-    s.update_blocks = large ? 3 : 4;
+    else if (size > 128 * MiB) s.stream_step = row >= (f32 ? 32 : 64);
+    else s.stream_step = size > 32 * MiB && row >= 64 && !ew;
+    s.stream_update = size > 64 * MiB;
+    s.stream_gbar = larger;
+    if (s.stream_step) s.step_blocks = row >= 16 ? 2 : 3;
+    else if (!large) s.step_blocks = !ew && size > 40 * MiB ? 4 : 0;
+    else if (ew) s.step_blocks = row >= 16 && (!f32 || larger) ? 2 : 3;
+    else s.step_blocks = row >= 16 ? 2 : 4;
+    s.stats_blocks = row < 16 || size <= 64 * MiB ? 0 : (f32 ? 3 : 4);
+    s.update_blocks = large ? 3 : s.stream_update ? 4 : 0;
     return s;
 }
 
