@@ -71,6 +71,60 @@ struct LaunchShape {
 // back to back; one step after a 1 GiB read that evicts the caches.  Layouts
 // without a name are layers of 2048 to 2.4 million elements.
 //
+// Streaming accesses to w and m.  Ordinary ones leave the new w and m as
+// dirty lines in the Infinity Cache.  If the next step finds them there (one
+// handle back to back, w and m fit) that saves HBM traffic; if other work
+// evicts them first (a training step's forward and backward passes, or
+// another handle), their write-backs are scattered among the reads of what
+// runs next, and the reads stall on the DRAM's turn-arounds: 204 MB of
+// writes that take 33 us by themselves cost 95 us within a K = 16 step and
+// 170 us within a K = 64 one.  Streaming accesses write straight through but
+// find nothing on the next step.  They are taken where their gain in turn
+// outweighs (in percent) what they lose back to back and after an eviction
+// (which leaves the ordinary accesses' write-backs out of the time); what is
+// lost back to back there is a chosen loss.  Ordinary -> streaming:
+//   row >= 64 (K = 16 fp32, 32 bf16): from 8 MiB on.  8 MiB fp32 23 -> 23;
+//     21 -> 22; 26 -> 26, 24 MiB fp32 52 -> 49; 50 -> 48; 55 -> 52, bf16 52
+//     -> 52; 51 -> 50; 56 -> 55, 85 MiB bf16 177 -> 167; 167 -> 165; 182 ->
+//     179; ResNet-50 (195 MiB) bf16 K = 32 384 -> 357; 341 -> 360; 360 ->
+//     362, K = 64 679 -> 651; 633 -> 655; 646 -> 659, fp32 K = 16 392 ->
+//     352; 340 -> 355; 361 -> 361;
+//   row 32 to 63, fp32: from 128 MiB on.  K = 8 85 MiB 95 -> 97; 89 -> 95;
+//     98 -> 102, 112 MiB 133 -> 122; 113 -> 121; 125 -> 127, 144 MiB 171 ->
+//     155; 141 -> 154; 157 -> 162, ResNet-50 235 -> 207; 190 -> 209; 213 ->
+//     214, VGG-16's size (1056 MiB) 1145 -> 1060; 1086 -> 1057; 1112 -> 1063;
+//   row 32 to 63, bf16, and 16 to 31, fp32: from 512 MiB on.  K = 16 bf16
+//     ResNet-50 230 -> 215; 188 -> 214; 213 -> 219, 280 MiB 325 -> 313; 283
+//     -> 313; 313 -> 317, 450 MiB 517 -> 500; 475 -> 499; 508 -> 503, 600
+//     MiB 686 -> 670; 649 -> 671; 679 -> 677, 1056 MiB 1179 -> 1162; 1144
+//     -> 1169; 1171 -> 1170; K = 4 fp32 195 MiB 153 -> 140; 123 -> 140; 135
+//     -> 146, 280 MiB 206 -> 195; 182 -> 196; 194 -> 200, 450 MiB 322 ->
+//     312; 302 -> 308; 311 -> 318, 600 MiB 425 -> 407; 402 -> 405; 408 -> 418;
+//   row < 16: fp32 once w and m outgrow the cache (K = 1 230 MiB 116 -> 105;
+//     97 -> 104; 101 -> 110, 280 MiB at the two blocks per CU that were best
+//     before 139 -> 125; 131 -> 125; 130 -> 129, 1056 MiB 478 -> 460; 466 ->
+//     464; 460 -> 447), bf16 never (K = 4 1056 MiB 573 -> 632; 531 -> 628;
+//     532 -> 630, nor with row 16 to 31: K = 8 768 -> 776; 739 -> 777; 733
+//     -> 776);
+//   element scales (w and m loads only, the stores always stream): bf16
+//     never (K = 16 195 MiB 280 -> 269; 239 -> 270; 262 -> 277, 1056 MiB 1349
+//     -> 1405; 1328 -> 1395; 1343 -> 1396); fp32 row >= 64 from 128 MiB on
+//     (K = 16 85 MiB 171 -> 181; 169 -> 179; 179 -> 184, 144 MiB 322 -> 289;
+//     278 -> 288; 296 -> 295, 195 MiB 433 -> 388; 370 -> 383; 392 -> 387),
+//     32 to 63 from 512 MiB on (K = 8 195 MiB 262 -> 249; 223 -> 246; 246 ->
+//     252, 450 MiB 577 -> 554; 519 -> 560; 549 -> 555, 600 MiB 768 -> 746;
+//     714 -> 740; 730 -> 731, 1056 MiB 1325 -> 1289; 1265 -> 1295; 1288 ->
+//     1264), less never (K = 4 280 MiB 265 -> 257; 225 -> 257; 233 -> 265,
+//     1056 MiB 940 -> 944; 911 -> 940; 918 -> 967).
+// LARS's update has just one row (the mean) beside w and m: from 64 MiB on.
+// K = 8 fp32 56 MiB 79 -> 78; 76 -> 78; 83 -> 82, 72 MiB 98 -> 93; 92 -> 93;
+// 98 -> 98; K = 16 bf16 56 MiB 86 -> 86; 82 -> 86; 90 -> 92, 72 MiB 107 ->
+// 104; 101 -> 105; 107 -> 108, 195 MiB 270 -> 255; 246 -> 249; 245 -> 254.
+// The mean itself streams once it alone outgrows the cache (w and m: 512
+// MiB).  K = 8 fp32 480 MiB 596 -> 580; 556 -> 581; 564 -> 581, 560 MiB 705
+// -> 673; 687 -> 675; 695 -> 682; K = 16 bf16 480 MiB 641 -> 632; 612 ->
+// 622; 618 -> 632, 560 MiB 742 -> 726; 736 -> 718; 743 -> 723.
+//
 // Blocks per CU.  Fewer resident blocks mean fewer row streams open at once
 // (K + 2 per block), so the DRAM rows are used better, until too few reads
 // are in flight; small layouts, whose blocks the chip holds at once, only
@@ -110,36 +164,6 @@ struct LaunchShape {
 //     483 -> 482; 480 -> 479; 486 -> 482, 1056 MiB 1297 -> 1275; 1312 -> 1289;
 //     1321 -> 1280).
 //
-// Streaming accesses to w and m.  Ordinary ones leave the new w and m as
-// dirty lines in the Infinity Cache.  If the next step finds them there (one
-// handle stepping back to back, w and m fit) that saves HBM traffic; if other
-// work evicts them first (a training step's forward and backward passes, or
-// another handle), their write-backs are scattered among the reads of what
-// runs next, and the reads stall on the DRAM's turn-arounds: 204 MB of
-// writes that take 33 us by themselves cost 95 us within a K = 16 step and
-// 170 us within a K = 64 one.  Streaming accesses write straight through but
-// find nothing on the next step.  Both sides measured, kernel alone (us),
-// ordinary -> streaming, handles in turn; back to back:
-//   fit: ResNet-50 bf16 K = 4 107 -> 114; 93 -> 112, K = 8 143 -> 136; 117
-//     -> 134, K = 16 220 -> 205; 177 -> 203 (ordinary); K = 32 373 -> 345;
-//     330 -> 342, K = 64 667 -> 635; 618 -> 634; fp32 K = 4 144 -> 132; 117
-//     -> 133 (ordinary), K = 8 224 -> 194; 180 -> 194; ResNet-18 fp32 K = 8
-//     86 -> 88; 82 -> 87 (ordinary), K = 16 151 -> 144; 145 -> 142;
-//   larger: VGG-16 fp32 K = 1 468 -> 446; 435 -> 446, K = 4 718 -> 684; 694
-//     -> 692, K = 8 1155 -> 1056; 1089 -> 1050; bf16 K = 1 425 -> 447, K = 4
-//     553 -> 607, K = 8 754 -> 749; 726 -> 739 (ordinary), K = 16 1132 ->
-//     1108; 1096 -> 1110;
-//   element scales (w and m loads; the stores always stream): bf16 ResNet-50
-//     K = 16 253 -> 244; 215 -> 243, K = 4 145 -> 157, VGG-16 K = 16 1293 ->
-//     1355 (ordinary); fp32 ResNet-50 K = 8 246 -> 231; 210 -> 230, VGG-16
-//     K = 8 1335 -> 1299; 1334 -> 1277; ResNet-18 K = 16 161 -> 169 (ordinary).
-// LARS's update has just one row (the mean) beside w and m: the whole LARS
-// step ResNet-50 K = 16 bf16 258 -> 238; 232 -> 235, K = 8 180 -> 167; 164
-// -> 166, ResNet-18 K = 8 fp32 112 -> 107; 102 -> 107.  The mean itself
-// streams once it alone outgrows the cache (VGG-16 K = 8 fp32 1365 -> 1312,
-// bf16 986 -> 930; ResNet-50, where it is read back from the cache, 238 ->
-// 243).
-//
 // The grouped tile order (tile_of_block) serves every kernel but the step
 // kernel with element scales of bf16 replicas, whose four fp32 streams
 // outweigh the rows: grouped against dispatch order (kernel alone, in turn)
@@ -153,10 +177,11 @@ inline LaunchShape launch_shape(const ags_config& c) {
     constexpr int64_t MiB = 1 << 20;
     LaunchShape s;
     s.grouped_step = f32 || !ew;
-    if (ew && !f32) s.stream_step = false;
-    else if (large) s.stream_step = f32 || row >= 32;
-    else if (size > 128 * MiB) s.stream_step = row >= (f32 ? 32 : 64);
-    else s.stream_step = size > 32 * MiB && row >= 64 && !ew;
+    if (ew) s.stream_step = f32 && (row >= 64 ? size > 128 * MiB : row >= 32 && larger);
+    else if (row >= 64) s.stream_step = size > 8 * MiB;
+    else if (row >= 32) s.stream_step = f32 ? size > 128 * MiB : larger;
+    else if (row >= 16) s.stream_step = f32 && larger;
+    else s.stream_step = f32 && large;
     s.stream_update = size > 64 * MiB;
     s.stream_gbar = larger;
     if (s.stream_step) s.step_blocks = row >= 16 ? 2 : 3;

@@ -50,3 +50,30 @@ def test_small_layouts_are_not_capped(shapes):
     cases = [(64 * MIB, K, dt, 0, 1) for K in REPLICAS for dt in ("f32", "bf16")]
     for c, s in zip(cases, shapes(cases)):
         assert s.stats_blocks == 0 and s.update_blocks == 0, (c, s)
+
+
+@pytest.mark.parametrize("K,dtype,ew,line", [
+    (16, "f32", 0, 8), (1024, "f32", 0, 8), (32, "bf16", 0, 8), (64, "bf16", 0, 8),
+    (8, "f32", 0, 128), (15, "f32", 0, 128), (16, "bf16", 0, 512), (31, "bf16", 0, 512),
+    (4, "f32", 0, 512), (7, "f32", 0, 512), (1, "f32", 0, 256), (3, "f32", 0, 256),
+    (1, "bf16", 0, None), (15, "bf16", 0, None),
+    (16, "f32", 1, 128), (8, "f32", 1, 512), (15, "f32", 1, 512),
+    (7, "f32", 1, None), (1, "f32", 1, None), (64, "bf16", 1, None), (1024, "bf16", 1, None)])
+def test_streaming_is_taken_from_its_line_on(shapes, K, dtype, ew, line):
+    """w and m are streamed only above the size from which that was measured
+    to gain more, with other states in between, than it loses back to back."""
+    sizes = [MIB, 8 * MIB, 64 * MIB, 128 * MIB, 195 * MIB, 256 * MIB, 280 * MIB, 450 * MIB, 512 * MIB,
+             600 * MIB, 1056 * MIB]
+    if line is not None:
+        sizes += [line * MIB, line * MIB + 8]
+    cases = [(b, K, dtype, ew, 0) for b in sizes]
+    for c, s in zip(cases, shapes(cases)):
+        assert bool(s.stream_step) == (line is not None and c[0] > line * MIB), (c, s)
+
+
+def test_lars_streams_from_its_lines_on(shapes):
+    """The update's w and m above 64 MiB, the mean once it outgrows the cache."""
+    for line, field in ((64, "stream_update"), (512, "stream_gbar")):
+        cases = [(line * MIB + d, K, dt, 0, 1) for d in (0, 8) for K in REPLICAS for dt in ("f32", "bf16")]
+        for c, s in zip(cases, shapes(cases)):
+            assert bool(getattr(s, field)) == (c[0] > line * MIB), (c, s)
