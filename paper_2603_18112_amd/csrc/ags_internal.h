@@ -279,11 +279,15 @@ struct StepArgs {
     int* corr_count;         // how many
     int updated;             // the step kernel applied predicted coefficients
     // Step kernel: tiles in reverse order.  Once w and m outgrow the
-    // Infinity Cache the host alternates the direction from step to step,
-    // so that a step starts on the lines the step before touched last
-    // instead of sweeping a working set larger than the cache in one
-    // direction (VGG-16 K = 8 fp32 warm step 1079 -> 1038 us, elementwise
-    // 1250 -> 1207 us; layouts that fit the cache gain nothing).
+    // Infinity Cache the host alternates the direction from step to step, so
+    // that a step starts on the lines the step before touched last instead of
+    // sweeping a working set larger than the cache in one direction.  One
+    // direction / alternating, whole step, ordinary accesses to w and m, back
+    // to back: VGG-16 K = 8 bf16 754 / 725 us, with element scales 957 / 941,
+    // 300 MiB of w and m K = 8 bf16 224 / 208 (in turn the same); streaming
+    // ones leave less to find: VGG-16 K = 8 fp32 1090 / 1091 back to back,
+    // 1069 / 1061 in turn, with element scales 1302 / 1292 both ways.  Layouts
+    // that fit the cache gain nothing.
     int reverse;
     unsigned* done_count;    // layers finished (reset by the last block)
     const FinChunk* chunks;  // finalize blocks
