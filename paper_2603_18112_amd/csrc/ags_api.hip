@@ -48,10 +48,8 @@ struct WsLayout {
 size_t elem_bytes(ags_dtype dt) { return dt == AGS_BF16 ? 2 : 4; }
 
 bool materialize_gbar(const ags_config& c) {
-    // Only a LARS step has a second pass over the replica mean.  Keep it when
-    // re-reading the replicas there would cost more than writing and reading
-    // one fp32 per element.
-    return c.mode == AGS_MODE_LARS && (size_t)c.K * elem_bytes(c.grad_dtype) > 8;
+    // Only a LARS step has a second pass over the replica mean.
+    return c.mode == AGS_MODE_LARS && ags::keeps_mean(c.K * (int)elem_bytes(c.grad_dtype));
 }
 
 // stats_only: the pieces a statistics-only call uses (no replica mean kept

@@ -193,6 +193,23 @@ inline LaunchShape launch_shape(const ags_config& c) {
     return s;
 }
 
+// The replica counts with kernels of their own; 0 for any other (then K >= 3).
+constexpr int compiled_replicas(int K) {
+    return K == 1 || K == 2 || K == 4 || K == 8 || K == 16 || K == 32 || K == 64 ? K : 0;
+}
+// Does a LARS step keep the replica mean between its passes?  When re-reading
+// the replicas there would cost more than writing and reading one fp32 per
+// element.
+constexpr bool keeps_mean(int row_bytes) { return row_bytes > 8; }
+// What launch_shape and keeps_mean can ask of the kernels of a compiled
+// replica count (or of any other, kt = 0); only those are built.
+constexpr bool can_stream_step(bool f32, int kt, bool ew) {
+    if (ew) return f32 && (kt == 0 || kt >= 8);
+    return f32 || kt == 0 || kt >= 16;
+}
+constexpr bool can_keep_mean(bool f32, int kt) { return kt == 0 || keeps_mean(kt * (f32 ? 4 : 2)); }
+constexpr bool can_drop_mean(bool f32, int kt) { return !keeps_mean((kt ? kt : 3) * (f32 ? 4 : 2)); }
+
 // Elements per tile of a layer of numel elements.
 __host__ __device__ inline int64_t tile_elems_for(int64_t numel) {
     const int64_t per = (int64_t)kTileElems * kMaxTilesPerLayer;

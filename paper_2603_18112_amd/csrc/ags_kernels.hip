@@ -1346,55 +1346,74 @@ hipError_t launch(void (*k)(A), dim3 grid, dim3 block, hipStream_t s, const A& a
 }
 
 
+// A combination that launch_shape and keeps_mean cannot ask for has no kernel
+// and is an error.
 template <typename GT, int KT, int RMODE>
 hipError_t step_r(const StepArgs& a, int n_tiles, bool update, hipStream_t s, KernelEvents ev) {
     const dim3 grid(n_tiles), block(kTileBlock);
     const unsigned lds = (unsigned)a.lds_pad;
+    constexpr bool F32 = sizeof(GT) == 4;
     if (!update) {
-        if (a.gbar && a.stream_gbar) {
-            if (a.w_norm_in)
-                return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 2>, grid, block, s, a, ev, lds);
-            return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 2>, grid, block, s, a, ev, lds);
+        if constexpr (can_keep_mean(F32, KT)) {
+            if (a.gbar && a.stream_gbar) {
+                if (a.w_norm_in)
+                    return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 2>, grid, block, s, a, ev, lds);
+                return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 2>, grid, block, s, a, ev, lds);
+            }
+            if (a.gbar) {
+                if (a.w_norm_in)
+                    return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 1>, grid, block, s, a, ev, lds);
+                return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 1>, grid, block, s, a, ev, lds);
+            }
         }
-        if (a.gbar) {
-            if (a.w_norm_in)
-                return launch(step_kernel<GT, KT, RMODE, false, false, false, true, 1>, grid, block, s, a, ev, lds);
-            return launch(step_kernel<GT, KT, RMODE, false, false, false, false, 1>, grid, block, s, a, ev, lds);
-        }
+        if (a.gbar) return hipErrorInvalidValue;
         if (a.w_norm_in)
             return launch(step_kernel<GT, KT, RMODE, false, false, false, true>, grid, block, s, a, ev, lds);
         return launch(step_kernel<GT, KT, RMODE, false, false, false>, grid, block, s, a, ev, lds);
     }
-    if (a.ew) {
-        if (a.stream_wm) return launch(step_kernel<GT, KT, RMODE, true, true, true>, grid, block, s, a, ev, lds);
-        return launch(step_kernel<GT, KT, RMODE, true, true, false>, grid, block, s, a, ev, lds);
+    if (a.stream_wm) {
+        if constexpr (can_stream_step(F32, KT, true)) {
+            if (a.ew) return launch(step_kernel<GT, KT, RMODE, true, true, true>, grid, block, s, a, ev, lds);
+        }
+        if constexpr (can_stream_step(F32, KT, false)) {
+            if (!a.ew) return launch(step_kernel<GT, KT, RMODE, true, false, true>, grid, block, s, a, ev, lds);
+        }
+        return hipErrorInvalidValue;
     }
-    if (a.stream_wm) return launch(step_kernel<GT, KT, RMODE, true, false, true>, grid, block, s, a, ev, lds);
+    if (a.ew) return launch(step_kernel<GT, KT, RMODE, true, true, false>, grid, block, s, a, ev, lds);
     return launch(step_kernel<GT, KT, RMODE, true, false, false>, grid, block, s, a, ev, lds);
 }
 
 template <typename GT, int KT>
 hipError_t step_k(const StepArgs& a, int n_tiles, bool update, hipStream_t s, KernelEvents ev) {
-    const int rm = a.small_replica == 0 ? 0 : (a.small_replica < 0 ? 1 : 2);
-    if (rm == 0) return step_r<GT, KT, 0>(a, n_tiles, update, s, ev);
-    if (rm == 1) return step_r<GT, KT, 1>(a, n_tiles, update, s, ev);
-    return step_r<GT, KT, 2>(a, n_tiles, update, s, ev);
+    if (a.small_replica == 0) return step_r<GT, KT, 0>(a, n_tiles, update, s, ev);
+    if (a.small_replica < 0) return step_r<GT, KT, 1>(a, n_tiles, update, s, ev);
+    if constexpr (KT != 1) return step_r<GT, KT, 2>(a, n_tiles, update, s, ev);
+    return hipErrorInvalidValue;
 }
 
 template <typename GT, int KT>
 hipError_t update_k(const UpdateArgs& a, hipStream_t s, KernelEvents ev) {
     const dim3 grid(a.n_tiles), block(kTileBlock);
     const unsigned lds = (unsigned)a.lds_pad;
-    if (!a.gbar) {
-        if (a.w_norm_out) return launch(update_kernel<GT, KT, true, true, false>, grid, block, s, a, ev, lds);
-        return launch(update_kernel<GT, KT, true, false, false>, grid, block, s, a, ev, lds);
+    constexpr bool F32 = sizeof(GT) == 4;
+    if constexpr (can_drop_mean(F32, KT)) {
+        if (!a.gbar) {
+            if (a.w_norm_out) return launch(update_kernel<GT, KT, true, true, false>, grid, block, s, a, ev, lds);
+            return launch(update_kernel<GT, KT, true, false, false>, grid, block, s, a, ev, lds);
+        }
     }
-    if (a.stream_wm) {
-        if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, true>, grid, block, s, a, ev, lds);
-        return launch(update_kernel<GT, KT, false, false, true>, grid, block, s, a, ev, lds);
+    if constexpr (can_keep_mean(F32, KT)) {
+        if (a.gbar && a.stream_wm) {
+            if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, true>, grid, block, s, a, ev, lds);
+            return launch(update_kernel<GT, KT, false, false, true>, grid, block, s, a, ev, lds);
+        }
+        if (a.gbar) {
+            if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, false>, grid, block, s, a, ev, lds);
+            return launch(update_kernel<GT, KT, false, false, false>, grid, block, s, a, ev, lds);
+        }
     }
-    if (a.w_norm_out) return launch(update_kernel<GT, KT, false, true, false>, grid, block, s, a, ev, lds);
-    return launch(update_kernel<GT, KT, false, false, false>, grid, block, s, a, ev, lds);
+    return hipErrorInvalidValue;
 }
 
 template <typename GT, int KT>
@@ -1404,7 +1423,7 @@ hipError_t correct_k(const UpdateArgs& a, hipStream_t s, KernelEvents ev) {
 }
 
 #define AGS_K_DISPATCH(FN, GT, K, ...)           \
-    switch (K) {                                 \
+    switch (compiled_replicas(K)) {              \
         case 1: return FN<GT, 1>(__VA_ARGS__);   \
         case 2: return FN<GT, 2>(__VA_ARGS__);   \
         case 4: return FN<GT, 4>(__VA_ARGS__);   \

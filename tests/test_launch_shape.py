@@ -2,6 +2,7 @@
 is host code in a header, compiled here into a small program)."""
 import collections
 import os
+import re
 import subprocess
 
 import pytest
@@ -77,3 +78,39 @@ def test_lars_streams_from_its_lines_on(shapes):
         cases = [(line * MIB + d, K, dt, 0, 1) for d in (0, 8) for K in REPLICAS for dt in ("f32", "bf16")]
         for c, s in zip(cases, shapes(cases)):
             assert bool(getattr(s, field)) == (c[0] > line * MIB), (c, s)
+
+
+def test_the_library_holds_exactly_the_kernels_that_can_be_launched(shapes):
+    """Every instantiation of the step, update and correction kernels against
+    what the rule, the kept replica mean (more than 8 replica bytes per
+    element), carried weight norms and the small-batch choice can ask for."""
+    from paper_2603_18112_amd import ags
+    ags.load_library()
+    nm = subprocess.run(["nm", "-C", _build.LIB], capture_output=True, text=True, check=True).stdout
+    built = {m.group(1) for m in re.finditer(r"__device_stub__((?:step|update|correct)_kernel<[^>]*>)", nm)}
+
+    lines = [8, 40, 64, 128, 256, 512]
+    sizes = [MIB, 2048 * MIB] + [b * MIB + d for b in lines for d in (0, 8)]
+    cases = [(b, K, dt, ew, lars) for b in sizes for K in sorted({*REPLICAS, *range(1, 70)})
+             for dt in ("f32", "bf16") for ew, lars in ((0, 0), (1, 0), (0, 1))]
+
+    def name(kernel, *args):
+        return f"{kernel}_kernel<{', '.join(str(a).lower() for a in args)}>"
+
+    want = set()
+    for (_, K, dt, ew, lars), s in zip(cases, shapes(cases)):
+        gt = "float" if dt == "f32" else "unsigned short"
+        kt = K if K in (1, 2, 4, 8, 16, 32, 64) else 0
+        keep = K * (4 if dt == "f32" else 2) > 8
+        for r in range(3 if K > 1 else 2):
+            want.add(name("step", gt, kt, r, False, False, False, False, 0))  # ags_stats
+            if not lars:
+                want.add(name("step", gt, kt, r, True, bool(ew), bool(s.stream_step), False, 0))
+                continue
+            for carried in (False, True):
+                want.add(name("step", gt, kt, r, False, False, False, carried, 0))
+                want.add(name("step", gt, kt, r, False, False, False, carried,
+                              0 if not keep else 2 if s.stream_gbar else 1))
+                want.add(name("update", gt, kt, not keep, carried, keep and bool(s.stream_update)))
+        want.add(name("correct", gt, kt))
+    assert built == want, (sorted(built - want), sorted(want - built))
