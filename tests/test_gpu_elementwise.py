@@ -8,6 +8,7 @@ element scale of every layer.
 import numpy as np
 import pytest
 
+import streaming_cases
 from ags_parity import Pair, check_scales, log, run_steps, to_device
 from paper_2603_18112_amd import ags, layouts, synth
 
@@ -73,19 +74,25 @@ def test_resnet50_k16_bf16_three_steps():
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_streaming_variant_above_the_cache_sized_working_set(dtype):
-    # 13.1M elements: w, m and the two scale buffers (16 bytes per element)
-    # pass 192 MiB, so the step kernel takes its non-temporal variant; ragged
-    # layers and one large one, every flag combination.
+def test_one_large_layer_and_ragged_ones(dtype):
+    # 13.1M elements: one large layer beside ragged ones, every flag
+    # combination; the scales, w and m are stored non-temporally and w and m
+    # loaded with ordinary accesses.
     sizes = [13_000_000, 7, 2049, 20003, 63, 77_777, 1]
     flags = [SD, layouts.LAYER_SCALE, 0, layouts.LAYER_DECAY, SD, SD, 0]
     lay = layouts.custom_layout(sizes, flags, pad=8)
-    assert 16 * lay.n_flat > 192 << 20
-    run_steps(lay, 4, 3, dtype=dtype, elementwise=True, label=f"ew streaming {dtype}")
+    run_steps(lay, 4, 3, dtype=dtype, elementwise=True, label=f"ew large and ragged {dtype}")
+
+
+@pytest.mark.parametrize("case", streaming_cases.ELEMENT_SCALES, ids=streaming_cases.name)
+def test_streamed_w_and_m_at_ragged_ends(case):
+    mib, K, dtype, hyper = case
+    run_steps(streaming_cases.layout(mib), K, 2, dtype=dtype, elementwise=True, check_each=False,
+              label=f"ew streamed {streaming_cases.name(case)}", **hyper)
 
 
 def test_vgg16_k8_two_steps():
-    # The largest layout: streaming accesses, the XCD-aware tile order and
+    # The largest layout: streaming accesses, the grouped tile order and
     # fp32 replicas at full size (138M elements, 67,569 tiles).
     lay = layouts.get_layout("vgg16")
     run_steps(lay, 8, 2, check_each=False, elementwise=True, stride=layouts.replica_stride(lay),

@@ -11,6 +11,7 @@ import math
 import numpy as np
 import pytest
 
+import streaming_cases
 from ags_parity import Pair, check_params, check_stats, log, run_steps, to_device
 from oracle import OracleAGS
 from paper_2603_18112_amd import ags, layouts, synth
@@ -1018,3 +1019,16 @@ def test_an_elements_update_does_not_depend_on_where_its_layer_ends(K, dtype, el
         h.close()
         out.append((w.view(n, 2048)[:, :2047], m.view(n, 2048)[:, :2047]))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("case", streaming_cases.STEP + streaming_cases.LARS, ids=streaming_cases.name)
+def test_streamed_w_and_m_at_ragged_ends(case):
+    """Layouts just above the size from which w and m (and LARS's mean) are
+    streamed, with layers that end within a group, for compiled and runtime
+    replica counts and every small-batch choice."""
+    mib, K, dtype, hyper = case
+    hyper = dict(hyper)
+    if case in streaming_cases.LARS:
+        hyper["mode"] = "lars"
+    run_steps(streaming_cases.layout(mib), K, 2, dtype=dtype, check_each=False,
+              label=f"streamed {streaming_cases.name(case)}", **hyper)

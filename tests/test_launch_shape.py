@@ -114,3 +114,19 @@ def test_the_library_holds_exactly_the_kernels_that_can_be_launched(shapes):
                 want.add(name("update", gt, kt, not keep, carried, keep and bool(s.stream_update)))
         want.add(name("correct", gt, kt))
     assert built == want, (sorted(built - want), sorted(want - built))
+
+
+def test_the_streaming_parity_cases_stream(shapes):
+    """The layouts with which the GPU tests check the streaming kernels are
+    above the lines from which they are taken (and not far above)."""
+    import streaming_cases as sc
+
+    def ask(cases, lars):
+        return shapes([(8 * sc.layout(mib).n_flat, K, dt, int(cases is sc.ELEMENT_SCALES), lars)
+                       for mib, K, dt, _ in cases])
+
+    assert all(s.stream_step for s in ask(sc.STEP, 0))
+    assert all(s.stream_step for s in ask(sc.ELEMENT_SCALES, 0))
+    lars = ask(sc.LARS, 1)
+    assert all(s.stream_update for s in lars) and lars[-1].stream_gbar
+    assert all(K * (4 if dt == "f32" else 2) > 8 for _, K, dt, _ in sc.LARS)  # the mean is kept
