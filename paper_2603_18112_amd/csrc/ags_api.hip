@@ -1211,6 +1211,10 @@ __global__ __launch_bounds__(256) void noalloc_tables_kernel(NoallocTables t) {
 // often than that).
 constexpr int kTableBlocks = 512;
 
+// Records (80 bytes per layer) that ags_stats_noalloc brings back by way of
+// the stack: 818 layers.
+constexpr size_t kRecStack = 64 << 10;
+
 }  // namespace
 
 extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w, const void* d_grads,
@@ -1349,13 +1353,6 @@ extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w,
     sa.lds_pad = lds_pad_for(dev, ags::launch_shape(c).stats_blocks);
     sa.grouped = 1;
 
-    std::vector<char> rec;
-    try {
-        rec.resize(wl.rec_bytes);
-    } catch (const std::bad_alloc&) {
-        why = "host allocation failed";
-        return fail(AGS_E_NOMEM);
-    }
     e = hipMemcpyAsync(sp, c.layers, (size_t)c.n_layers * sizeof(ags_layer), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(noalloc_tables_kernel, dim3(std::min(c.n_layers, kTableBlocks)), dim3(256), 0,
@@ -1364,17 +1361,27 @@ extern "C" ags_status ags_stats_noalloc(const ags_config* cfg, const float* d_w,
     }
     if (e == hipSuccess) e = ags::launch_step(sa, c.grad_dtype, (int)n_tiles, false, s, ags::KernelEvents{});
     if (e == hipSuccess) e = ags::launch_finalize(sa, (int)n_chunks, s, ags::KernelEvents{});
-    // One copy (the records are contiguous): a copy to pageable memory waits
-    // for the stream and costs some 10 us of its own.
+    // The records are contiguous: up to kRecStack bytes come back in one copy
+    // (a copy to pageable memory waits for the stream and costs some 10 us of
+    // its own), more of them straight to the caller's two places, so that
+    // nothing is allocated on the host either.
+    alignas(16) char rec[kRecStack];
+    const size_t layer_bytes = (size_t)c.n_layers * sizeof(ags_layer_stats);
+    const bool staged = wl.rec_bytes <= kRecStack;
     if (e == hipSuccess)
-        e = hipMemcpyAsync(rec.data(), ws + wl.lstats, wl.rec_bytes, hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(staged ? static_cast<void*>(rec) : out_layers, ws + wl.lstats,
+                           staged ? wl.rec_bytes : layer_bytes, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && !staged)
+        e = hipMemcpyAsync(out_global, ws + wl.gstats, sizeof(ags_global_stats), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         why = std::string("ags_stats_noalloc: ") + hipGetErrorString(e);
         (void)hipGetLastError();
         return fail(AGS_E_DEVICE);
     }
-    std::memcpy(out_layers, rec.data(), (size_t)c.n_layers * sizeof(ags_layer_stats));
-    std::memcpy(out_global, rec.data() + (wl.gstats - wl.lstats), sizeof(ags_global_stats));
+    if (staged) {
+        std::memcpy(out_layers, rec, layer_bytes);
+        std::memcpy(out_global, rec + (wl.gstats - wl.lstats), sizeof(ags_global_stats));
+    }
     return AGS_OK;
 }

@@ -127,11 +127,12 @@ def test_noalloc_random_configs_match_ags_stats():
         del g, w, m
 
 
-@pytest.mark.parametrize("n_layers", [1, 511, 512, 513, 1025])
+@pytest.mark.parametrize("n_layers", [1, 511, 512, 513, 818, 819, 1025])
 def test_noalloc_tables_with_layers_sharing_blocks(n_layers):
     """Layer counts around the 512 blocks that build the tables (then several
-    layers share a block, and the last blocks may have none), layers of one to
-    three tiles: bitwise equal to a handle's ags_stats."""
+    layers share a block, and the last blocks may have none) and around the 818
+    whose records come back in one copy, layers of one to three tiles: bitwise
+    equal to a handle's ags_stats."""
     import torch
     sizes = [1 + (1237 * l) % 4300 for l in range(n_layers)]
     lay = layouts.custom_layout(sizes, pad=8)
@@ -151,3 +152,20 @@ def test_noalloc_tables_with_layers_sharing_blocks(n_layers):
     for f in ags.LAYER_STATS_FIELDS:
         assert np.array_equal(nl[f], s.layer[f]), (n_layers, f)
     assert ng == s.glob
+
+
+def test_noalloc_allocates_no_record_buffer_on_the_host(tmp_path):
+    """12,000 layers' records take 960,040 bytes: no C++ allocation of that
+    order happens within the call (a small program whose operator new notes
+    the largest size it was asked for)."""
+    import os
+    import subprocess
+    from paper_2603_18112_amd import _build
+    exe = str(tmp_path / "largest_new")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "noalloc_largest_new.cpp")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                    "-I", _build.INCLUDE, src, _build.LIB, "-L/opt/rocm/lib", "-lamdhip64",
+                    f"-Wl,-rpath,{_build.LIBDIR}:/opt/rocm/lib", "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert int(r.stdout) < 100_000
