@@ -357,9 +357,10 @@ struct UpdateArgs {
     // per CU, and its streaming accesses to w and m (launch_shape).
     int lds_pad;
     int stream_wm;
-    // LARS update: the tiles in reverse order (the last tiles first).  The pass then ends on the first tiles, whose replica mean
-    // the next statistics pass writes first, and those lines are still in
-    // the Infinity Cache: that pass measured 154.4 -> 151.0 us (ResNet-50
+    // LARS update: the tiles in reverse order (the last tiles first).  The
+    // pass then ends on the first tiles, whose replica mean the next
+    // statistics pass writes first, and those lines are still in the Infinity
+    // Cache: that pass measured 154.4 -> 151.0 us (ResNet-50
     // K = 16 bf16; K = 64 582 -> 574 us) with the update pass unchanged.
     // Used while w and m fit the cache (VGG-16's step lost 0.8% with it).
     int reverse;

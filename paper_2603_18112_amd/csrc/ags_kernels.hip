@@ -23,8 +23,10 @@
 // bf16 gradients lane l owns [8l, 8l+8), one 16-byte load per replica row.
 // Reductions
 // run in a fixed order (per thread, wave butterfly, the four waves in index
-// order, then per layer in fp64 over tiles in index order); the one atomic
-// only counts finished layers, so a step is bitwise reproducible.
+// order, then per layer in fp64 over tiles in index order).  The atomics count
+// finished chunks and layers and give listed layers their place on the
+// correction list, whose order does not matter, so a step is bitwise
+// reproducible.
 #include <math.h>
 
 #include <type_traits>
@@ -642,7 +644,9 @@ __device__ Sum4 sum_tiles(const StepArgs& a, int tb, int te, Sum4* sh, bool ew_r
 // kernel took (MI355X, before -> now): 161 layers of ResNet-50 10.4 -> 8.8
 // us, 62 of ResNet-18 8.2 -> 6.9, 300 of a generic model 14.7 -> 9.3, VGG-16
 // (a layer of 13 chunks) 13.9 -> 11.3; a kernel that does nothing takes 4.5 there.
-// All of a thread's tile partials loaded in one go measured the same.
+// Not kept: all 16 tile partials of a thread loaded in one go (a tiny CNN 6.5
+// -> 6.8 us, ResNet-18 6.9 -> 7.8, ResNet-50 8.8 -> 9.1, 300 layers 9.3 ->
+// 9.5, VGG-16 11.2 either way).
 //
 // Delta = |G - G_prev| / G_prev, infinite on a first step, when G_prev <= 0
 // or when a value is not finite; sensitive = !(Delta < delta); Delta_l

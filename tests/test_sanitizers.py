@@ -4,8 +4,8 @@
 * libags's host code (argument validation, workspace layout, state and
   planner), built by hipcc with the sanitizers on the host pass only and
   without the step, finalize, correction and update kernels (launcher
-  stubs stand in for them; the two table kernels of the no-alloc entry
-  point, which live beside the host code, are compiled for the GPU without
+  stubs stand in for them; the table kernel of the no-alloc entry point,
+  which lives beside the host code, is compiled for the GPU without
   sanitizers), runs the C-ABI and planner tests.
 
 Each run is a subprocess with the matching sanitizer runtime preloaded; a
