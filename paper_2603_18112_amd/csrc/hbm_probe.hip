@@ -10,22 +10,23 @@
 //         tile, the lane mapping of the step kernel.  Its rate is the
 //         ceiling of that access pattern on this GPU: what a kernel moving
 //         exactly those bytes, with no statistics, sustains.  It is timed
-//         warm (50 launches back to back) and cold (each launch alone after
+//         warm (30 launches back to back) and cold (each launch alone after
 //         a 1 GiB read with ordinary loads, which evicts the L2s and the
 //         Infinity Cache).
 //         With "ew", the pattern of elementwise AGS: also the element scale
 //         in force read and the refreshed one written (8 more bytes).
 //         Both are timed with every number of blocks per CU from the
-//         register limit down to 2 (a dynamic LDS pad caps it), in both
-//         tile orders the step kernel uses (round-robin over the XCDs, and
-//         a contiguous range per XCD) and with load batches of 8 and 16
-//         (bf16 rows, or fp32 half rows) or, for bf16 rows, two batches of
-//         4 or 8 pipelined as the step kernel does, with w and m loaded
-//         before the replicas or after the first batch, and (warm) with the
-//         tile direction alternating from launch to launch as the step
-//         kernel's does for large layouts, and the fastest counts: how many
-//         streams run at once, and where, decides how well the DRAM rows
-//         are used.
+//         register limit down to 2 (a dynamic LDS pad caps it), in three
+//         tile orders (round-robin over the XCDs, and the step kernel's
+//         groups of 8 tiles per XCD, and a contiguous range per XCD), with
+//         ordinary and with streaming accesses to w and m, and with load
+//         batches of 8 and 16 (bf16 rows, or fp32 half rows) or, for bf16
+//         rows, two batches of 4 or 8 pipelined as the step kernel does,
+//         with w and m loaded before the replicas or after the first batch,
+//         and (warm) with the tile direction alternating from launch to
+//         launch as the step kernel's does for large layouts, and the
+//         fastest counts: how many streams run at once, and where, decides
+//         how well the DRAM rows are used.
 // Usage: hbm_probe [K grad_dtype(bf16|f32) n_elements [ew]]; without
 // arguments the step pattern is the ResNet-50 layout's (K = 16, bf16,
 // 25,557,032).
@@ -102,35 +103,48 @@ __device__ __forceinline__ void add_bf16x8(const u32x4& v, float (&s)[8]) {
     }
 }
 
+constexpr int kReverse = 4;  // in probe_step's order
+
+__device__ __forceinline__ float4 stream_load4(const float* p) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                       __uint_as_float(v.w));
+}
+
 // One block per tile of kTile elements; lane l of wave v owns, for bf16
 // rows, elements [512v + 8l, +8) (one 16-byte load per row), for fp32 rows
 // [512v + 4l, +4) and [512v + 256 + 4l, +4) (two 16-byte loads per row).
 // Rows are loaded in batches of B (bf16: B rows; fp32: B / 2 rows, two
 // loads each) before any is used.  B = -KB (bf16 only, K a multiple of
 // 2 KB): two batches of KB rows in registers, the next batch's loads in
-// flight while the current one is summed.  With xcd, block b
-// takes the tile that the step kernel's XCD-aware order gives it (each of
-// the 8 XCDs, which receive every 8th block, walks a contiguous range of
-// tiles) instead of tile b; with xcd & 2 the tiles run in reverse order.  w and m: the same
-// elements, fp32, read and written.  EW (element scales): one more fp32
-// stream read (sc_in) and one written (sc_out) for the same elements, with
-// ordinary accesses (EW = 1) or streaming ones, w and m stores included
-// (EW = 2).  WL: w, m (and the scale in force) are loaded after the first
-// replica batch's loads are issued instead of before them.  n is a
+// flight while the current one is summed.  Block b takes tile b
+// (order 0), a tile of its XCD's contiguous range (1; the 8 XCDs receive
+// every 8th block each) or, as the step kernel does, a tile of its XCD's 8
+// consecutive ones in a run of 64 (2); with kReverse the tiles run in reverse
+// order.  w and m: the same elements, fp32, read and written, with ordinary
+// or (NT) streaming accesses.  EW (element scales): one more fp32 stream
+// read (sc_in) and one written (sc_out) for the same elements, with ordinary
+// accesses (EW = 1) or streaming ones, w and m stores included (EW = 2; NT
+// is then their loads).  WL: w, m (and the scale in force) are loaded after
+// the first replica batch's loads are issued instead of before them.  n is a
 // multiple of kTile.
-template <bool BF16, int EW, int B, bool WL>
+template <bool BF16, int EW, bool NT, int B, bool WL>
 __global__ __launch_bounds__(256) void probe_step(const void* __restrict__ grads, size_t stride,
                                                   int K, float* __restrict__ w,
                                                   float* __restrict__ m,
                                                   const float* __restrict__ sc_in,
-                                                  float* __restrict__ sc_out, int xcd) {
+                                                  float* __restrict__ sc_out, int order) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int tile = blockIdx.x;
-    if (xcd & 1) {
-        const int n = gridDim.x, q = n / 8, r = n % 8, x = tile % 8, i = tile / 8;
+    const int n = gridDim.x;
+    if ((order & 3) == 1) {
+        const int q = n / 8, r = n % 8, x = tile % 8, i = tile / 8;
         tile = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
+    } else if ((order & 3) == 2) {
+        const int o = tile % 64, run = tile - o;
+        if (run + 64 <= n) tile = run + (o % 8) * 8 + o / 8;
     }
-    if (xcd & 2) tile = (int)gridDim.x - 1 - tile;  // reverse direction
+    if (order & kReverse) tile = n - 1 - tile;
     const size_t base = (size_t)tile * kTile + (size_t)wave * 512;
     const size_t i0 = base + (BF16 ? 8 * lane : 4 * lane);
     const size_t i1 = BF16 ? i0 + 4 : i0 + 256;
@@ -140,18 +154,23 @@ __global__ __launch_bounds__(256) void probe_step(const void* __restrict__ grads
     // The compiler keeps the chosen order: scheduling barriers around it.
     auto load_wm = [&]() {
         __builtin_amdgcn_sched_barrier(0);
-        w0 = *reinterpret_cast<const float4*>(w + i0);
-        w1 = *reinterpret_cast<const float4*>(w + i1);
-        m0 = *reinterpret_cast<const float4*>(m + i0);
-        m1 = *reinterpret_cast<const float4*>(m + i1);
+        if (NT) {
+            w0 = stream_load4(w + i0);
+            w1 = stream_load4(w + i1);
+            m0 = stream_load4(m + i0);
+            m1 = stream_load4(m + i1);
+        } else {
+            w0 = *reinterpret_cast<const float4*>(w + i0);
+            w1 = *reinterpret_cast<const float4*>(w + i1);
+            m0 = *reinterpret_cast<const float4*>(m + i0);
+            m1 = *reinterpret_cast<const float4*>(m + i1);
+        }
         if (EW == 1) {
             c0 = *reinterpret_cast<const float4*>(sc_in + i0);
             c1 = *reinterpret_cast<const float4*>(sc_in + i1);
         } else if (EW == 2) {
-            const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(sc_in + i0));
-            const u32x4 b = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(sc_in + i1));
-            c0 = make_float4(__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w));
-            c1 = make_float4(__uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w));
+            c0 = stream_load4(sc_in + i0);
+            c1 = stream_load4(sc_in + i1);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -233,12 +252,14 @@ __global__ __launch_bounds__(256) void probe_step(const void* __restrict__ grads
     w0.z = fmaf(-1e-3f, m0.z, w0.z); w0.w = fmaf(-1e-3f, m0.w, w0.w);
     w1.x = fmaf(-1e-3f, m1.x, w1.x); w1.y = fmaf(-1e-3f, m1.y, w1.y);
     w1.z = fmaf(-1e-3f, m1.z, w1.z); w1.w = fmaf(-1e-3f, m1.w, w1.w);
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
     if (EW == 2) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
         const f32x4 sa = {c0.x * 0.5f, c0.y * 0.5f, c0.z * 0.5f, c0.w * 0.5f};
         const f32x4 sb = {c1.x * 0.5f, c1.y * 0.5f, c1.z * 0.5f, c1.w * 0.5f};
         __builtin_nontemporal_store(sa, reinterpret_cast<f32x4*>(sc_out + i0));
         __builtin_nontemporal_store(sb, reinterpret_cast<f32x4*>(sc_out + i1));
+    }
+    if (EW == 2 || NT) {
         __builtin_nontemporal_store((f32x4){w0.x, w0.y, w0.z, w0.w}, reinterpret_cast<f32x4*>(w + i0));
         __builtin_nontemporal_store((f32x4){w1.x, w1.y, w1.z, w1.w}, reinterpret_cast<f32x4*>(w + i1));
         __builtin_nontemporal_store((f32x4){m0.x, m0.y, m0.z, m0.w}, reinterpret_cast<f32x4*>(m + i0));
@@ -255,11 +276,22 @@ __global__ __launch_bounds__(256) void probe_step(const void* __restrict__ grads
     *reinterpret_cast<float4*>(m + i1) = m1;
 }
 
-// Launch of the step pattern: element scales or not (ew: 0, 1 or 2), with
-// lds bytes of dynamic LDS (unused, a cap on the blocks per CU), in the
-// XCD-aware tile order or not, with the load schedule `sched`: batches of
-// 8 (0) or 16 (1), or (bf16 only, see pipelined_ok) two pipelined batches
-// of 4 (2) or 8 (3); plus 4 for w and m after the first batch.
+// Launch of the step pattern with the accesses `acc` (kAccess), with lds
+// bytes of dynamic LDS (unused, a cap on the blocks per CU), in the tile
+// order `order`, with the load schedule `sched`: batches of 8 (0) or 16 (1),
+// or (bf16 only, see pipelined_ok) two pipelined batches of 4 (2) or 8 (3);
+// plus 4 for w and m after the first batch.
+struct Access {
+    int ew;      // element scales: 0 none, 1 ordinary, 2 streaming
+    bool nt;     // streaming w and m
+    const char* name;
+};
+constexpr Access kAccess[] = {{0, false, "ordinary w and m"},
+                              {0, true, "streaming w and m"},
+                              {1, false, "ordinary w, m and scales"},
+                              {2, false, "streaming scales and stores, ordinary w and m loads"},
+                              {2, true, "streaming w, m and scales"}};
+constexpr const char* kOrder[] = {"dispatch", "range per XCD", "groups of 8 per XCD"};
 constexpr int kScheds = 8;
 constexpr const char* kSchedName[kScheds] = {
     "8", "16", "2x4 pipelined", "2x8 pipelined", "8, w and m after the first batch",
@@ -269,41 +301,42 @@ bool pipelined_ok(bool bf16, int K, int sched) {
     const int sc = sched & 3, kb = sc == 2 ? 4 : 8;
     return sc < 2 || (bf16 && K % (2 * kb) == 0);
 }
-void launch_step_pattern(bool bf16, int ew, int grid, const void* g, size_t stride, int K, float* w,
-                         float* m, const float* sc_in, float* sc_out, unsigned lds, int xcd,
-                         int sched) {
-#define PROBE_LAUNCH(BF, E, B)                                                                     \
-    do {                                                                                           \
-        if (sched >= 4)                                                                            \
-            hipLaunchKernelGGL((probe_step<BF, E, B, true>), dim3(grid), dim3(256), lds, 0, g, stride, \
-                               K, w, m, sc_in, sc_out, xcd);                                       \
-        else                                                                                       \
-            hipLaunchKernelGGL((probe_step<BF, E, B, false>), dim3(grid), dim3(256), lds, 0, g,       \
-                               stride, K, w, m, sc_in, sc_out, xcd);                               \
-    } while (0)
-#define PROBE_SCHED(BF, E)                    \
-    do {                                      \
-        if ((sched & 3) == 1) PROBE_LAUNCH(BF, E, 16); \
-        else PROBE_LAUNCH(BF, E, 8);          \
-    } while (0)
-#define PROBE_SCHED_PIPE(E)                         \
-    do {                                            \
-        if ((sched & 3) == 3) PROBE_LAUNCH(true, E, -8);  \
-        else if ((sched & 3) == 2) PROBE_LAUNCH(true, E, -4); \
-        else PROBE_SCHED(true, E);                  \
-    } while (0)
-    if (bf16) {
-        if (ew == 0) PROBE_SCHED_PIPE(0);
-        else if (ew == 1) PROBE_SCHED_PIPE(1);
-        else PROBE_SCHED_PIPE(2);
-    } else {
-        if (ew == 0) PROBE_SCHED(false, 0);
-        else if (ew == 1) PROBE_SCHED(false, 1);
-        else PROBE_SCHED(false, 2);
+template <bool BF16, int EW, bool NT, int B>
+void launch_b(int grid, const void* g, size_t stride, int K, float* w, float* m, const float* sc_in,
+              float* sc_out, unsigned lds, int order, int sched) {
+    if (sched >= 4)
+        hipLaunchKernelGGL((probe_step<BF16, EW, NT, B, true>), dim3(grid), dim3(256), lds, 0, g, stride,
+                           K, w, m, sc_in, sc_out, order);
+    else
+        hipLaunchKernelGGL((probe_step<BF16, EW, NT, B, false>), dim3(grid), dim3(256), lds, 0, g, stride,
+                           K, w, m, sc_in, sc_out, order);
+}
+template <bool BF16, int EW, bool NT>
+void launch_s(int grid, const void* g, size_t stride, int K, float* w, float* m, const float* sc_in,
+              float* sc_out, unsigned lds, int order, int sched) {
+    const int sc = sched & 3;
+    if constexpr (BF16) {
+        if (sc == 3) return launch_b<true, EW, NT, -8>(grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
+        if (sc == 2) return launch_b<true, EW, NT, -4>(grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
     }
-#undef PROBE_SCHED_PIPE
-#undef PROBE_SCHED
-#undef PROBE_LAUNCH
+    if (sc == 1) return launch_b<BF16, EW, NT, 16>(grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
+    launch_b<BF16, EW, NT, 8>(grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
+}
+template <bool BF16, typename... A>
+void launch_a(int acc, A... a) {
+    switch (acc) {
+        case 0: return launch_s<BF16, 0, false>(a...);
+        case 1: return launch_s<BF16, 0, true>(a...);
+        case 2: return launch_s<BF16, 1, false>(a...);
+        case 3: return launch_s<BF16, 2, false>(a...);
+        default: return launch_s<BF16, 2, true>(a...);
+    }
+}
+void launch_step_pattern(bool bf16, int acc, int grid, const void* g, size_t stride, int K, float* w,
+                         float* m, const float* sc_in, float* sc_out, unsigned lds, int order,
+                         int sched) {
+    if (bf16) launch_a<true>(acc, grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
+    else launch_a<false>(acc, grid, g, stride, K, w, m, sc_in, sc_out, lds, order, sched);
 }
 
 #define CHECK(x)                                                                  \
@@ -430,75 +463,61 @@ int main(int argc, char** argv) {
             ++n_pads;
         }
     }
-    // With element scales, the faster of ordinary and streaming accesses for
-    // the scale streams (and the w and m stores) is the pattern's rate.
-    // Warm launches also run with the direction alternating from launch to
-    // launch (zig), as the step kernel does once w and m outgrow the
-    // Infinity Cache.
-    int best_ew = ew ? 1 : 0, best_pad = 0, best_xcd = 0, best_deep = 0, best_zig = 0;
-    double step_us = 0;
-    for (int v = ew ? 1 : 0; v <= (ew ? 2 : 0); ++v) {
-        for (int c = 0; c < 4 * kScheds * n_pads; ++c) {
-            const int pi = c % n_pads, xcd = (c / n_pads) & 1, deep = (c / (2 * n_pads)) % kScheds,
-                      zig = c / (2 * kScheds * n_pads);
-            if (!pipelined_ok(bf16, K, deep)) continue;
-            double us = 0;
-            int calls = 0;
-            const int rc = time_launches(
-                [&]() {
-                    const int dir = (zig && (calls++ & 1)) ? 2 : 0;
-                    launch_step_pattern(bf16, v, grid, g, stride, K, w, m, sc_in, sc_out, pads[pi],
-                                        xcd | dir, deep);
-                },
-                50, e0, e1, &us);
-            if (rc) return rc;
-            if (step_us == 0 || us < step_us) {
-                step_us = us;
-                best_ew = v;
-                best_pad = pi;
-                best_xcd = xcd;
-                best_deep = deep;
-                best_zig = zig;
-            }
-        }
-    }
-    // The same pattern cold: each launch timed on its own after a 1 GiB read
-    // that evicts the L2s and the 256 MB Infinity Cache (median of 21).
+    // Every launch shape; the fastest is the pattern's rate.  Warm launches
+    // also run with the direction alternating from launch to launch (zig), as
+    // the step kernel does once w and m outgrow the Infinity Cache.
+    struct Pick {
+        double us;
+        int acc, pad, order, sched, zig;
+    } warm{}, cold{};
     const size_t evict_bytes = (size_t)1 << 30;
     u32x4* evict = nullptr;
     CHECK(hipMalloc(&evict, evict_bytes));
     if (fill(evict, evict_bytes, 6u, 1)) return 1;
     CHECK(hipDeviceSynchronize());
-    constexpr int kCold = 21;
-    double cold_us = 0;
-    int best_cold_pad = 0, best_cold_xcd = 0, best_cold_deep = 0;
-    for (int ci = 0; ci < 2 * kScheds * n_pads; ++ci) {
-        const int pi = ci % n_pads, xcd = (ci / n_pads) & 1, deep = ci / (2 * n_pads);
-        if (!pipelined_ok(bf16, K, deep)) continue;
-        float cold_ms[kCold];
-        for (int r = 0; r < kCold; ++r) {
-            hipLaunchKernelGGL(evict_read, dim3(2048), dim3(256), 0, 0, evict, evict_bytes / 16, out);
-            CHECK(hipEventRecord(e0));
-            launch_step_pattern(bf16, best_ew, grid, g, stride, K, w, m, sc_in, sc_out, pads[pi], xcd, deep);
-            CHECK(hipEventRecord(e1));
-            CHECK(hipEventSynchronize(e1));
-            CHECK(hipGetLastError());
-            CHECK(hipEventElapsedTime(&cold_ms[r], e0, e1));
-        }
-        for (int i = 1; i < kCold; ++i)  // insertion sort, then the median
-            for (int j = i; j > 0 && cold_ms[j] < cold_ms[j - 1]; --j) {
-                const float t = cold_ms[j];
-                cold_ms[j] = cold_ms[j - 1];
-                cold_ms[j - 1] = t;
-            }
-        const double us = cold_ms[kCold / 2] * 1e3;
-        if (cold_us == 0 || us < cold_us) {
-            cold_us = us;
-            best_cold_pad = pi;
-            best_cold_xcd = xcd;
-            best_cold_deep = deep;
-        }
-    }
+    constexpr int kWarm = 30, kCold = 21;
+    for (int acc = ew ? 2 : 0; acc <= (ew ? 4 : 1); ++acc)
+        for (int order = 0; order < 3; ++order)
+            for (int sched = 0; sched < kScheds; ++sched)
+                for (int pi = 0; pi < n_pads; ++pi) {
+                    if (!pipelined_ok(bf16, K, sched)) continue;
+                    for (int zig = 0; zig < 2; ++zig) {
+                        double us = 0;
+                        int calls = 0;
+                        const int rc = time_launches(
+                            [&]() {
+                                const int dir = (zig && (calls++ & 1)) ? kReverse : 0;
+                                launch_step_pattern(bf16, acc, grid, g, stride, K, w, m, sc_in, sc_out,
+                                                    pads[pi], order | dir, sched);
+                            },
+                            kWarm, e0, e1, &us);
+                        if (rc) return rc;
+                        if (warm.us == 0 || us < warm.us) warm = Pick{us, acc, pi, order, sched, zig};
+                    }
+                    // The same cold: each launch timed on its own after a
+                    // 1 GiB read that evicts the L2s and the 256 MB Infinity
+                    // Cache (median of 21).
+                    float cold_ms[kCold];
+                    for (int r = 0; r < kCold; ++r) {
+                        hipLaunchKernelGGL(evict_read, dim3(2048), dim3(256), 0, 0, evict, evict_bytes / 16,
+                                           out);
+                        CHECK(hipEventRecord(e0));
+                        launch_step_pattern(bf16, acc, grid, g, stride, K, w, m, sc_in, sc_out, pads[pi],
+                                            order, sched);
+                        CHECK(hipEventRecord(e1));
+                        CHECK(hipEventSynchronize(e1));
+                        CHECK(hipGetLastError());
+                        CHECK(hipEventElapsedTime(&cold_ms[r], e0, e1));
+                    }
+                    for (int i = 1; i < kCold; ++i)  // insertion sort, then the median
+                        for (int j = i; j > 0 && cold_ms[j] < cold_ms[j - 1]; --j) {
+                            const float t = cold_ms[j];
+                            cold_ms[j] = cold_ms[j - 1];
+                            cold_ms[j - 1] = t;
+                        }
+                    const double us = cold_ms[kCold / 2] * 1e3;
+                    if (cold.us == 0 || us < cold.us) cold = Pick{us, acc, pi, order, sched, 0};
+                }
     CHECK(hipFree(evict));
     const size_t bpe = (size_t)K * es + 16 + (ew ? 8 : 0);
     const double step_bytes = (double)ne * (double)bpe;
@@ -506,20 +525,19 @@ int main(int argc, char** argv) {
            "\"step_pattern_GBps\": %.1f, \"step_pattern_us\": %.2f, "
            "\"step_pattern_cold_GBps\": %.1f, \"step_pattern_cold_us\": %.2f, "
            "\"step_pattern_blocks_per_cu\": %d, \"step_pattern_cold_blocks_per_cu\": %d, "
-           "\"step_pattern_xcd_order\": %s, \"step_pattern_cold_xcd_order\": %s, "
+           "\"step_pattern_tile_order\": \"%s\", \"step_pattern_cold_tile_order\": \"%s\", "
            "\"step_pattern_alternating\": %s, "
+           "\"step_pattern_accesses\": \"%s\", \"step_pattern_cold_accesses\": \"%s\", "
            "\"step_pattern_load_batch\": \"%s\", \"step_pattern_cold_load_batch\": \"%s\", "
            "\"step_pattern\": "
            "{\"K\": %d, \"grad_dtype\": \"%s\", \"elements\": %zu, \"bytes_per_element\": %zu, "
            "\"element_scales\": %s}, "
            "\"bytes\": %zu, \"data\": \"random\"}\n",
-           best[0], best_grid[0], best[1], best_grid[1], step_bytes / (step_us * 1e-6) / 1e9, step_us,
-           step_bytes / (cold_us * 1e-6) / 1e9, cold_us, caps[best_pad], caps[best_cold_pad],
-           best_xcd ? "true" : "false", best_cold_xcd ? "true" : "false", best_zig ? "true" : "false",
-           kSchedName[best_deep],
-           kSchedName[best_cold_deep], K,
-           bf16 ? "bf16" : "f32", ne, bpe,
-           !ew ? "null" : (best_ew == 2 ? "\"streaming\"" : "\"ordinary\""), bytes);
+           best[0], best_grid[0], best[1], best_grid[1], step_bytes / (warm.us * 1e-6) / 1e9, warm.us,
+           step_bytes / (cold.us * 1e-6) / 1e9, cold.us, caps[warm.pad], caps[cold.pad],
+           kOrder[warm.order], kOrder[cold.order], warm.zig ? "true" : "false", kAccess[warm.acc].name,
+           kAccess[cold.acc].name, kSchedName[warm.sched], kSchedName[cold.sched], K,
+           bf16 ? "bf16" : "f32", ne, bpe, ew ? "true" : "false", bytes);
     if (sc) CHECK(hipFree(sc));
     CHECK(hipFree(g));
     CHECK(hipFree(w));
