@@ -430,15 +430,17 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 s2[e] = 0.0f;
             }
         };
+        // Groups of four from replica 1 on, the last one of 1 to 4 replicas,
+        // which is summed first.
+        const int left = ((K - 2) & 3) + 1, last = K - left;  // K >= 3 here
         int k = 1;
-        const int left = ((K - 2) & 3) + 1;  // K >= 3 here
         if constexpr (FULL) {
-            // Replica 0 and the 1 to 4 replicas left over beside whole fours
-            // in one round trip, then eights (bf16) and fours.  (Replica 0,
-            // the fours and each replica left over had a round trip of their
-            // own, six for K = 12 instead of two: ResNet-50 K = 12 bf16
-            // step 203 -> 190 us, K = 3 bf16 VGG-16's three round trips are
-            // now one.  fp32 eights would hold 64 registers of loads.)
+            // Replica 0 and the last group in one round trip, then eights
+            // (bf16) and fours.  (Replica 0, the fours and each replica left
+            // over had a round trip of their own, six for K = 12 instead of
+            // two: ResNet-50 K = 12 bf16 step 203 -> 190 us, K = 3 bf16
+            // VGG-16's three round trips are now one.  fp32 eights would hold
+            // 64 registers of loads.)
             auto sum = [&](const auto& x, int k0, auto from, auto to) {
 #pragma unroll
                 for (int j = decltype(from)::value; j < decltype(to)::value; ++j) {
@@ -456,19 +458,18 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 r0.load(g + idx);
 #pragma unroll
                 for (int j = 0; j < decltype(n)::value; ++j)
-                    x[j].load(g + (int64_t)(1 + j) * stride + idx);
+                    x[j].load(g + (int64_t)(last + j) * stride + idx);
                 r0.widen(g0);
                 shift();
-                sum(x, 1, C0{}, n);
+                sum(x, last, C0{}, n);
             };
             if (left == 1) head(std::integral_constant<int, 1>{});
             else if (left == 2) head(std::integral_constant<int, 2>{});
             else if (left == 3) head(std::integral_constant<int, 3>{});
             else head(C4{});
-            k += left;
             if constexpr (sizeof(GT) == 2) {
 #pragma unroll 1
-                for (; k + 7 < K; k += 8) {
+                for (; k + 7 < last; k += 8) {
                     RawGroup<GT> x[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) x[j].load(g + (int64_t)(k + j) * stride + idx);
@@ -477,27 +478,29 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 }
             }
 #pragma unroll 1
-            for (; k + 3 < K; k += 4) {
+            for (; k < last; k += 4) {
                 RawGroup<GT> x[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) x[j].load(g + (int64_t)(k + j) * stride + idx);
                 sum(x, k, C0{}, C4{});
             }
         } else {
-            // The ragged end (one group of a layer at most), in the full
-            // groups' batches: an element's mean has the same bits wherever
+            // The ragged end (one group of a layer at most), in the same
+            // groups and order: an element's mean has the same bits wherever
             // its layer ends.
-            int end = k + left;
+            int from = last, to = K, next = 1;
 #pragma unroll 1
-            while (k < K) {
+            while (true) {
 #pragma unroll 1
-                for (; k < end; ++k) {
+                for (int j = from; j < to; ++j) {
                     float x[kVec];
-                    load_tail<GT, Map<GT>::HS>(g + (int64_t)k * stride + idx, n0, n1, x);
-                    acc(k, x);
+                    load_tail<GT, Map<GT>::HS>(g + (int64_t)j * stride + idx, n0, n1, x);
+                    acc(j, x);
                 }
                 flush();
-                end += 4;
+                if (next >= last) break;
+                from = next;
+                to = next += 4;
             }
         }
         const double dK = (double)K;

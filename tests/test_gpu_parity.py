@@ -1032,3 +1032,30 @@ def test_streamed_w_and_m_at_ragged_ends(case):
         hyper["mode"] = "lars"
     run_steps(streaming_cases.layout(mib), K, 2, dtype=dtype, check_each=False,
               label=f"streamed {streaming_cases.name(case)}", **hyper)
+
+
+@pytest.mark.parametrize("K", [3, 5, 6, 7, 12, 18, 21, 30])
+def test_runtime_replica_counts_sum_groups_of_four_from_replica_1_on(K):
+    """The replica mean of a count without a kernel of its own: fp32 sums of
+    the differences to replica 0 over groups of four, added in fp64.  The
+    groups decide the last bits, so they are pinned: with w = m = 0 and an
+    unscaled layer without decay m is the mean.  The fp64 sums are exact here
+    (random fp32 values of like exponents), whatever their order."""
+    import torch
+    n = 4096 + 5
+    rng = np.random.default_rng(K)
+    g = (rng.standard_normal((K, 4104)) + 3.0).astype(np.float32)
+    total = np.zeros(n)
+    for k0 in range(1, K, 4):
+        part = np.zeros(n, np.float32)
+        for k in range(k0, min(k0 + 4, K)):
+            part += g[k, :n] - g[0, :n]
+        total += part
+    mean = (g[0, :n].astype(np.float64) + total / K).astype(np.float32)
+    w = torch.zeros(4104, device="cuda")
+    m = torch.zeros_like(w)
+    h = ags.AGS([(0, n, 0)], w, m, K)
+    h.step(torch.from_numpy(g).cuda())
+    torch.cuda.synchronize()
+    h.close()
+    assert np.array_equal(m.cpu().numpy()[:n], mean)
