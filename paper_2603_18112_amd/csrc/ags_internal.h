@@ -52,6 +52,11 @@ constexpr int kXcdGroup = 8;
 #endif
 constexpr int64_t kOccupancyCapMinBytes = AGS_OCCUPANCY_CAP_MIN_BYTES;
 
+// Does a LARS step keep the replica mean between its passes?  When re-reading
+// the replicas there would cost more than writing and reading one fp32 per
+// element.
+constexpr bool keeps_mean(int row_bytes) { return row_bytes > 8; }
+
 // How the streaming kernels of a handle (or of a statistics call without
 // one) are launched: the most blocks that share a CU, 0 = as many as the
 // registers allow.
@@ -93,7 +98,13 @@ struct LaunchShape {
 //     98 -> 102, 112 MiB 133 -> 122; 113 -> 121; 125 -> 127, 144 MiB 171 ->
 //     155; 141 -> 154; 157 -> 162, ResNet-50 235 -> 207; 190 -> 209; 213 ->
 //     214, VGG-16's size (1056 MiB) 1145 -> 1060; 1086 -> 1057; 1112 -> 1063;
-//   row 32 to 63, bf16, and 16 to 31, fp32: from 512 MiB on.  K = 16 bf16
+//   row 40 to 63, bf16, and 20 to 31, fp32: once w and m outgrow the cache.
+//     K = 20 bf16 280 MiB 385 -> 360; 337 -> 362; 365 -> 366, 480 MiB 667 ->
+//     646; 620 -> 640; 650 -> 648, K = 24 280 MiB 446 -> 417; 396 -> 416; 425
+//     -> 421, K = 6 fp32 280 MiB 259 -> 239; 226 -> 239; 245 -> 243, 480 MiB
+//     431 -> 411; 396 -> 406; 416 -> 409; ResNet-50 K = 24 bf16 310 -> 285; 267
+//     -> 288; 287 -> 293;
+//   row 32 to 39, bf16, and 16 to 19, fp32: from 512 MiB on.  K = 16 bf16
 //     ResNet-50 230 -> 215; 188 -> 214; 213 -> 219, 280 MiB 325 -> 313; 283
 //     -> 313; 313 -> 317, 450 MiB 517 -> 500; 475 -> 499; 508 -> 503, 600
 //     MiB 686 -> 670; 649 -> 671; 679 -> 677, 1056 MiB 1179 -> 1162; 1144
@@ -111,11 +122,15 @@ struct LaunchShape {
 //     -> 1405; 1328 -> 1395; 1343 -> 1396); fp32 row >= 64 from 128 MiB on
 //     (K = 16 85 MiB 171 -> 181; 169 -> 179; 179 -> 184, 144 MiB 322 -> 289;
 //     278 -> 288; 296 -> 295, 195 MiB 433 -> 388; 370 -> 383; 392 -> 387),
-//     32 to 63 from 512 MiB on (K = 8 195 MiB 262 -> 249; 223 -> 246; 246 ->
-//     252, 450 MiB 577 -> 554; 519 -> 560; 549 -> 555, 600 MiB 768 -> 746;
-//     714 -> 740; 730 -> 731, 1056 MiB 1325 -> 1289; 1265 -> 1295; 1288 ->
-//     1264), less never (K = 4 280 MiB 265 -> 257; 225 -> 257; 233 -> 265,
-//     1056 MiB 940 -> 944; 911 -> 940; 918 -> 967).
+//     40 to 63 once w and m outgrow the cache (K = 10 195 MiB 303 -> 280; 257
+//     -> 280; 287 -> 285, 280 MiB 425 -> 397; 364 -> 395; 397 -> 395, 450 MiB
+//     667 -> 631; 601 -> 635; 638 -> 628), 24 to 39 from 512 MiB on (K = 8 195
+//     MiB 262 -> 249; 223 -> 246; 246 -> 252, 450 MiB 577 -> 554; 519 -> 560;
+//     549 -> 555, 600 MiB 768 -> 746; 714 -> 740; 730 -> 731, 1056 MiB 1325 ->
+//     1289; 1265 -> 1295; 1288 -> 1264, K = 7 280 MiB 351 -> 323; 290 -> 322;
+//     314 -> 327, 600 MiB 706 -> 675; 658 -> 672; 680 -> 678), less never (K =
+//     4 280 MiB 265 -> 257; 225 -> 257; 233 -> 265, 1056 MiB 940 -> 944; 911 ->
+//     940; 918 -> 967).
 // LARS's update has just one row (the mean) beside w and m: from 64 MiB on.
 // K = 8 fp32 56 MiB 79 -> 78; 76 -> 78; 83 -> 82, 72 MiB 98 -> 93; 92 -> 93;
 // 98 -> 98; K = 16 bf16 56 MiB 86 -> 86; 82 -> 86; 90 -> 92, 72 MiB 107 ->
@@ -130,12 +145,13 @@ struct LaunchShape {
 // are in flight; small layouts, whose blocks the chip holds at once, only
 // lose.
 //   Step kernel, ordinary accesses, w and m fit: 4 from 40 MiB on against no
-//     cap (bf16 K = 1 32 MiB 24.5 -> 24.9; 23.0 -> 23.1; 28.0 -> 28.0, fp32 K
-//     = 4 32 MiB 30.4 -> 30.9; 30.1 -> 30.4; 34.3 -> 34.6, bf16 K = 1 48 MiB
-//     31.7 -> 30.6; 30.7 -> 30.0; 35.1 -> 33.6, 195 MiB 96 -> 92; 84 -> 82;
-//     86 -> 83, bf16 K = 8 156 -> 152; 128 -> 125; 143 -> 141, K = 16 and
-//     fp32 within 1%); element scales: no cap (4 measures the same at every
-//     size, fp32 K = 8 and bf16 K = 16).
+//     cap (bf16 K = 1 32 MiB 24.5 -> 24.9; 23.0 -> 23.1; 28.0 -> 28.0, 48 MiB
+//     31.7 -> 30.6; 30.7 -> 30.0; 35.1 -> 33.6, 195 MiB 96 -> 92; 84 -> 82; 86
+//     -> 83, fp32 K = 4 32 MiB 30.4 -> 30.9; 30.1 -> 30.4; 34.3 -> 34.6, bf16
+//     K = 8 195 MiB 156 -> 152; 128 -> 125; 143 -> 141, K = 16 and fp32 within
+//     1%; element scales bf16 K = 1 32 MiB 31.3 -> 31.7; 30.7 -> 30.8; 35.0 ->
+//     35.4, 85 MiB 62.5 -> 61.5; 61.3 -> 60.2; 64.2 -> 63.5, 195 MiB 138 ->
+//     136; 123 -> 120; 125 -> 124, row >= 16 the same).
 //   Ordinary accesses, larger: row < 16 4 (bf16 K = 4 1056 MiB 573 -> 606 at
 //     2), else 2 against 4 (fp32 K = 4 280 MiB 216 -> 206; 175 -> 182; 187 ->
 //     194, 450 MiB 348 -> 322; 298 -> 302; 306 -> 311, bf16 K = 8 1056 MiB 768
@@ -159,10 +175,12 @@ struct LaunchShape {
 //     66.4, 1056 MiB 718 / 700 / 689; LARS's whole step 64 MiB 84.9 -> 86.0 at
 //     3, 85 MiB 108.2 -> 108.2, 195 MiB 238 -> 234) and 4 for bf16 (K = 8 64 MiB 34.1 / 34.9 / 36.8, 450 MiB
 //     184 / 180 / 187; K >= 16 the same).
-//   LARS update (whole step): from 64 MiB on 4 (K = 16 bf16 195 MiB 256 -> 252;
-//     250 -> 247; 256 -> 252, below the same), larger 3 (K = 8 fp32 400 MiB
-//     483 -> 482; 480 -> 479; 486 -> 482, 1056 MiB 1297 -> 1275; 1312 -> 1289;
-//     1321 -> 1280).
+//   LARS update (whole step): 4 from 64 MiB on, from 40 on where it reads the
+//     replicas again (row <= 8: K = 1 bf16 32 MiB 27.2 -> 27.2; 26.1 -> 26.1;
+//     31.1 -> 31.0, 48 MiB 35.3 -> 34.2; 34.4 -> 34.0; 40.3 -> 37.6; K = 4 fp32
+//     48 MiB 48.0 -> 48.0; 47.1 -> 48.4; 53.4 -> 53.5; K = 16 bf16 195 MiB 256
+//     -> 252; 250 -> 247; 256 -> 252); larger 3 (K = 8 fp32 400 MiB 483 -> 482;
+//     480 -> 479; 486 -> 482, 1056 MiB 1297 -> 1275; 1312 -> 1289; 1321 -> 1280).
 //
 // The grouped tile order (tile_of_block) serves every kernel but the step
 // kernel with element scales of bf16 replicas, whose four fp32 streams
@@ -177,19 +195,20 @@ inline LaunchShape launch_shape(const ags_config& c) {
     constexpr int64_t MiB = 1 << 20;
     LaunchShape s;
     s.grouped_step = f32 || !ew;
-    if (ew) s.stream_step = f32 && (row >= 64 ? size > 128 * MiB : row >= 32 && larger);
+    if (ew) s.stream_step = f32 && (row >= 64 ? size > 128 * MiB : row >= 40 ? large : row >= 24 && larger);
     else if (row >= 64) s.stream_step = size > 8 * MiB;
-    else if (row >= 32) s.stream_step = f32 ? size > 128 * MiB : larger;
-    else if (row >= 16) s.stream_step = f32 && larger;
+    else if (row >= 32 && f32) s.stream_step = size > 128 * MiB;
+    else if (row >= (f32 ? 20 : 40)) s.stream_step = large;
+    else if (row >= (f32 ? 16 : 32)) s.stream_step = larger;
     else s.stream_step = f32 && large;
     s.stream_update = size > 64 * MiB;
     s.stream_gbar = larger;
     if (s.stream_step) s.step_blocks = row >= 16 ? 2 : 3;
-    else if (!large) s.step_blocks = !ew && size > 40 * MiB ? 4 : 0;
+    else if (!large) s.step_blocks = size > 40 * MiB ? 4 : 0;
     else if (ew) s.step_blocks = row >= 16 && (!f32 || larger) ? 2 : 3;
     else s.step_blocks = row >= 16 ? 2 : 4;
     s.stats_blocks = row < 16 || size <= 64 * MiB ? 0 : (f32 ? 3 : 4);
-    s.update_blocks = large ? 3 : s.stream_update ? 4 : 0;
+    s.update_blocks = large ? 3 : size > (keeps_mean(row) ? 64 : 40) * MiB ? 4 : 0;
     return s;
 }
 
@@ -197,10 +216,6 @@ inline LaunchShape launch_shape(const ags_config& c) {
 constexpr int compiled_replicas(int K) {
     return K == 1 || K == 2 || K == 4 || K == 8 || K == 16 || K == 32 || K == 64 ? K : 0;
 }
-// Does a LARS step keep the replica mean between its passes?  When re-reading
-// the replicas there would cost more than writing and reading one fp32 per
-// element.
-constexpr bool keeps_mean(int row_bytes) { return row_bytes > 8; }
 // What launch_shape and keeps_mean can ask of the kernels of a compiled
 // replica count (or of any other, kt = 0); only those are built.
 constexpr bool can_stream_step(bool f32, int kt, bool ew) {
