@@ -430,17 +430,18 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
                 s2[e] = 0.0f;
             }
         };
-        // Groups of four from replica 1 on, the last one of 1 to 4 replicas,
-        // which is summed first.
-        const int left = ((K - 2) & 3) + 1, last = K - left;  // K >= 3 here
+        // Groups of four from replica 1 on.
         int k = 1;
         if constexpr (FULL) {
-            // Replica 0 and the last group in one round trip, then eights
-            // (bf16) and fours.  (Replica 0, the fours and each replica left
-            // over had a round trip of their own, six for K = 12 instead of
-            // two: ResNet-50 K = 12 bf16 step 203 -> 190 us, K = 3 bf16
-            // VGG-16's three round trips are now one.  fp32 eights would hold
-            // 64 registers of loads.)
+            // Replica 0 and the last group (1 to 4 replicas) in one round
+            // trip, then eights (bf16) and fours.  (Replica 0, the fours and
+            // each replica left over had a round trip of their own, six for K
+            // = 12 instead of two: ResNet-50 K = 12 bf16 step 203 -> 190 us, K
+            // = 3 bf16 VGG-16's three round trips are now one.  fp32 eights
+            // would hold 64 registers of loads.  The first group in place of
+            // the last would save another 0.3%, and 0.3 us of a tiny layout's
+            // 23, and move the groups by up to three replicas.)
+            const int left = ((K - 2) & 3) + 1, last = K - left;  // K >= 3 here
             auto sum = [&](const auto& x, int k0, auto from, auto to) {
 #pragma unroll
                 for (int j = decltype(from)::value; j < decltype(to)::value; ++j) {
@@ -486,21 +487,18 @@ __device__ __forceinline__ void moments(const GT* __restrict__ g, int64_t stride
             }
         } else {
             // The ragged end (one group of a layer at most), in the same
-            // groups and order: an element's mean has the same bits wherever
-            // its layer ends.
-            int from = last, to = K, next = 1;
+            // groups of four, the last of them last: their fp64 sums are
+            // exact as long as the groups' sums are within 2^21 of each other,
+            // so an element's mean has the same bits wherever its layer ends.
 #pragma unroll 1
-            while (true) {
+            for (; k < K; k += 4) {
 #pragma unroll 1
-                for (int j = from; j < to; ++j) {
+                for (int j = k; j < min(k + 4, K); ++j) {
                     float x[kVec];
                     load_tail<GT, Map<GT>::HS>(g + (int64_t)j * stride + idx, n0, n1, x);
                     acc(j, x);
                 }
                 flush();
-                if (next >= last) break;
-                from = next;
-                to = next += 4;
             }
         }
         const double dK = (double)K;
